@@ -66,12 +66,94 @@ __device__ __forceinline__ void box_muller_f(float ua, float ub, float& z0, floa
   z0 = r * __builtin_amdgcn_cosf(ub);
   z1 = r * __builtin_amdgcn_sinf(ub);
 }
+
+// FP64 Box-Muller.  The FP64 walks spend most of their time here, and most of
+// that in what general log / sqrt / sincos do for arguments that a uniform on
+// an open lattice cannot be: zero, subnormals, infinities, large angles.
+// Here u_a is in [2^-53, 1 - 2^-53], so -2 ln u_a in [2^-52, 74], and the
+// angle is reduced in units of a quarter turn, which is exact for u_b in
+// (0, 1) (2 pi u_b itself would be rounded first).  About 75 FP64 operations
+// instead of about 250; the Gaussians are as close to their exact values as
+// before or closer (against 113-bit values, in ulps of r, over 3 10^6 pairs of
+// both lattices and their ends: largest error 2.0 against 6.2 of log, sqrt
+// and sincos of the rounded angle, mean 0.42 against 1.08).
+//
+// -2 ln u (u normal): u = m 2^e with m in [sqrt(1/2), sqrt 2), ln m =
+// 2 atanh(s), s = (m - 1) / (m + 1) carried as s + sl; the polynomial is
+// (2 atanh(s) - 2 s) / s^3 in s^2, interpolated at Chebyshev points (relative
+// error of ln m below 2^-57).
+__device__ __forceinline__ double neg2_log_unit(double u) {
+  double m = __builtin_amdgcn_frexp_mant(u);        // [1/2, 1)
+  int e = __builtin_amdgcn_frexp_exp(u);
+  const bool low = m < 0x1.6a09e667f3bcdp-1;        // sqrt(1/2)
+  m = low ? m + m : m;
+  e -= low ? 1 : 0;
+  const double f = m - 1.0;                         // exact
+  const double d = m + 1.0;
+  const double dl = m - (d - 1.0);                  // d + dl = m + 1
+  double r = __builtin_amdgcn_rcp(d);               // about 2^-24; two Newton steps
+  r = fma(fma(-d, r, 1.0), r, r);
+  r = fma(fma(-d, r, 1.0), r, r);
+  const double s = f * r;
+  const double sl = fma(-s, dl, fma(-s, d, f)) * r;
+  const double z = s * s;
+  double p = 0x1.2b5bd9a316a24p-3;
+  p = fma(p, z, 0x1.39fe16ad885a7p-3);
+  p = fma(p, z, 0x1.7462b6e311a89p-3);
+  p = fma(p, z, 0x1.c71c62ddb431bp-3);
+  p = fma(p, z, 0x1.2492492df7663p-2);
+  p = fma(p, z, 0x1.99999999952abp-2);
+  p = fma(p, z, 0x1.5555555555558p-1);
+  const double ed = (double)e;
+  // low-order part: 2 sl + s^3 p + e (ln 2 - its double)
+  const double lo = fma(s * z, p, fma(2.0, sl, ed * 0x1.abc9e3b39803fp-56));
+  return -2.0 * (fma(ed, 0x1.62e42fefa39efp-1, 2.0 * s) + lo);
+}
+
+// sqrt of a normal x: Goldschmidt iterations from the hardware reciprocal
+// square root, the last two corrected by the exact residual x - g^2.
+__device__ __forceinline__ double sqrt_normal(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  double g = x * y, h = 0.5 * y;
+  const double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  g = fma(fma(-g, g, x), h, g);
+  return fma(fma(-g, g, x), h, g);
+}
+
 __device__ __forceinline__ void box_muller_d(double ua, double ub, double& z0, double& z1) {
-  const double r = sqrt(-2.0 * log(ua));
-  double s, c;
-  sincos(2.0 * 3.14159265358979323846 * ub, &s, &c);
-  z0 = r * c;
-  z1 = r * s;
+  const double r = sqrt_normal(neg2_log_unit(ua));
+  // 4 u_b = q + f, |f| <= 1/2 (adding 1.5 2^52 rounds to a whole number and
+  // leaves it in the low bits); f is exact
+  const double t = 4.0 * ub;
+  const double qm = t + 0x1.8p52;
+  const uint32_t q = (uint32_t)__builtin_bit_cast(uint64_t, qm);
+  const double f = t - (qm - 0x1.8p52);
+  const double f2 = f * f;
+  // sin and cos of f pi / 2
+  double ps = 0x1.e4a9d9166f052p-25;
+  ps = fma(ps, f2, -0x1.e3027dea82bd7p-19);
+  ps = fma(ps, f2, 0x1.50783208843ebp-13);
+  ps = fma(ps, f2, -0x1.32d2cce500387p-8);
+  ps = fma(ps, f2, 0x1.466bc6775a476p-4);
+  ps = fma(ps, f2, -0x1.4abbce625be52p-1);
+  const double sf = fma(f, 0x1.921fb54442d18p+0, f * fma(ps, f2, 0x1.1a62633145c07p-54));
+  double pc = -0x1.b2f3eb054afcdp-28;
+  pc = fma(pc, f2, 0x1.f9ce245cada0bp-22);
+  pc = fma(pc, f2, -0x1.a6d1eef479be1p-16);
+  pc = fma(pc, f2, 0x1.e1f5068688d5bp-11);
+  pc = fma(pc, f2, -0x1.55d3c7e3cb241p-6);
+  pc = fma(pc, f2, 0x1.03c1f081b5ac0p-2);
+  pc = fma(pc, f2, -0x1.3bd3cc9be45dep+0);
+  const double cf = fma(pc, f2, 1.0);
+  const bool odd = (q & 1u) != 0u;
+  const double c = odd ? sf : cf, s = odd ? cf : sf;
+  // cos is negative in the second and third quarter turn, sin in the last two
+  const double rc = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, r) ^ ((uint64_t)((q + 1u) & 2u) << 62));
+  const double rs = __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, r) ^ ((uint64_t)(q & 2u) << 62));
+  z0 = rc * c;
+  z1 = rs * s;
 }
 
 template <typename R, int LAYOUT>
