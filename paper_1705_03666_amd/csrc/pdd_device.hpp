@@ -66,6 +66,17 @@ __device__ __forceinline__ void box_muller_f(float ua, float ub, float& z0, floa
   z0 = r * __builtin_amdgcn_cosf(ub);
   z1 = r * __builtin_amdgcn_sinf(ub);
 }
+// FP64 Box-Muller from the library functions: for walk on spheres, whose jumps
+// amplify rounding differences (a path of 35 jumps turned two ulps of a
+// Gaussian into 8e-12 of its value), so that its paths follow the plain
+// formula's rounding.
+__device__ __forceinline__ void box_muller_libm(double ua, double ub, double& z0, double& z1) {
+  const double r = sqrt(-2.0 * log(ua));
+  double s, c;
+  sincos(2.0 * 3.14159265358979323846 * ub, &s, &c);
+  z0 = r * c;
+  z1 = r * s;
+}
 
 // FP64 Box-Muller.  The FP64 walks spend most of their time here, and most of
 // that in what general log / sqrt / sincos do for arguments that a uniform on
@@ -156,11 +167,12 @@ __device__ __forceinline__ void box_muller_d(double ua, double ub, double& z0, d
   z1 = rs * s;
 }
 
-template <typename R, int LAYOUT>
+// The Gaussians of one Philox block.  LIBM: box_muller_libm in FP64.
+template <typename R, int LAYOUT, bool LIBM = false>
 struct Normals;
 
-template <>
-struct Normals<float, RNG_QUAD24> {
+template <bool LIBM>
+struct Normals<float, RNG_QUAD24, LIBM> {
   static constexpr int kPerBlock = 4;
   __device__ __forceinline__ static void gen(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                              uint32_t k1, float* z) {
@@ -169,23 +181,29 @@ struct Normals<float, RNG_QUAD24> {
     box_muller_f(u24f(c2), u24f(c3), z[2], z[3]);
   }
 };
-template <>
-struct Normals<double, RNG_QUAD24> {
+template <bool LIBM>
+struct Normals<double, RNG_QUAD24, LIBM> {
   static constexpr int kPerBlock = 4;
   __device__ __forceinline__ static void gen(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                              uint32_t k1, double* z) {
     philox4x32_10(c0, c1, c2, c3, k0, k1);
-    box_muller_d(u24d(c0), u24d(c1), z[0], z[1]);
-    box_muller_d(u24d(c2), u24d(c3), z[2], z[3]);
+    if constexpr (LIBM) {
+      box_muller_libm(u24d(c0), u24d(c1), z[0], z[1]);
+      box_muller_libm(u24d(c2), u24d(c3), z[2], z[3]);
+    } else {
+      box_muller_d(u24d(c0), u24d(c1), z[0], z[1]);
+      box_muller_d(u24d(c2), u24d(c3), z[2], z[3]);
+    }
   }
 };
-template <>
-struct Normals<double, RNG_PAIR52> {
+template <bool LIBM>
+struct Normals<double, RNG_PAIR52, LIBM> {
   static constexpr int kPerBlock = 2;
   __device__ __forceinline__ static void gen(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
                                              uint32_t k1, double* z) {
     philox4x32_10(c0, c1, c2, c3, k0, k1);
-    box_muller_d(u52d(c0, c1), u52d(c2, c3), z[0], z[1]);
+    if constexpr (LIBM) box_muller_libm(u52d(c0, c1), u52d(c2, c3), z[0], z[1]);
+    else box_muller_d(u52d(c0, c1), u52d(c2, c3), z[0], z[1]);
   }
 };
 

@@ -122,7 +122,7 @@ __device__ __forceinline__ void batch_item(const LinearParams PDD_CONST_AS* P, c
                                            uint32_t* rec_n, int lane, ItemStat* __restrict__ istat,
                                            double* __restrict__ dump_phi, int64_t* __restrict__ dump_steps,
                                            const int64_t* __restrict__ dump_off) {
-  using NZr = Normals<R, LAYOUT>;
+  using NZr = Normals<R, LAYOUT, WOS>;
   using GS = GroupShape<DIM, NZr::kPerBlock>;
   constexpr int NM = GradedLex<DIM, kMaxPolyBCF>::N;
   const Dom<R> D = batch_dom<R>(P, false);

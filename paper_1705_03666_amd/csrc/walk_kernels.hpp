@@ -232,7 +232,7 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
        ItemStat* __restrict__ istat, double* __restrict__ igrad, int grad_stride,
        double* __restrict__ dump_phi, int64_t* __restrict__ dump_steps, const int64_t* __restrict__ dump_off,
        int refill_groups) {
-  using NZr = Normals<R, LAYOUT>;
+  using NZr = Normals<R, LAYOUT, WOS>;
   using GS = GroupShape<DIM, NZr::kPerBlock>;
   constexpr int NM = GradedLex<DIM, DFC>::N;
   constexpr int NT = (ADJ && TERMS) ? kAdjTerms : 0;
