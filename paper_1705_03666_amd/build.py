@@ -22,7 +22,7 @@ SOURCES = ["walk_fwd.hip", "walk_adj_f32.hip", "walk_adj_f64.hip", "walk_common.
            "walk_batch.hip", "noalloc.hip", "capi.cpp", "schedule.cpp", "specialize.cpp"]
 # device headers embedded into the library for runtime compilation of
 # problem-specialised kernels (see csrc/pdd_spec.hpp)
-RTC_HEADERS = ["pdd_internal.hpp", "pdd_device.hpp", "walk_kernels.hpp", "branch_kernels.hpp"]
+RTC_HEADERS = ["pdd_internal.hpp", "pdd_device.hpp", "walk_kernels.hpp", "walk_stream.hpp", "branch_kernels.hpp"]
 RTC_SOURCE = "rtc_sources.cpp"
 
 FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-I", os.path.join(ROOT, "include"), "-I", CSRC,

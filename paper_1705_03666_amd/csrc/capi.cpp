@@ -390,6 +390,7 @@ struct Plan {
   CallPtrs* d_call = nullptr;   // call block: CallPtrs, then the staging jobs
   StageJob* d_jobs = nullptr;
   int n_jobs = 0;
+  int max_job = 0;              // entries of the largest job
   std::vector<StageJob> jobs_host;   // graph plans: the staging jobs as captured,
   std::vector<JobSource> job_src;    // with where each one reads from
   double* d_nodes = nullptr;         // staged node coordinates
@@ -397,7 +398,11 @@ struct Plan {
   double* d_cd = nullptr;
   float* d_cf = nullptr;
   uint32_t* d_qhead = nullptr;
+  int n_qhead = 1;           // words to clear (a batch: kQueueStride per problem)
   ItemStat* d_istat = nullptr;
+  ItemStat* d_pstat = nullptr;  // items run in pieces: the pieces' statistics,
+  MergeJob* d_merge = nullptr;  // merged into the items' before the nodes'
+  int n_merge = 0;
   int64_t* d_first = nullptr;
   int64_t n_nodes = 0;
   bool has_out = false;
@@ -422,13 +427,12 @@ struct Plan {
 
   hipError_t enqueue(hipStream_t st) const {
     hipError_t e;
-    if ((e = launch_stage(d_jobs, n_jobs, d_perm, d_cd, d_cf, st)) != hipSuccess) return e;
+    if ((e = launch_stage(d_jobs, n_jobs, max_job, d_perm, d_cd, d_cf, d_qhead, n_qhead, st)) != hipSuccess) return e;
     if (plain) {
       for (const auto& L : pl)
         if ((e = (L.adjoint ? launch_plain_adj(L, st) : launch_plain(L, st))) != hipSuccess) return e;
       if (!adjoint) return launch_finalize_nodes(d_istat, d_first, n_nodes, d_call, 0, ctr, st);
     } else {
-      if ((e = launch_fill_u32(d_qhead, 1, 0u, st)) != hipSuccess) return e;
       if (bvp) {
         if ((e = launch_branch_bvp(bvl, st)) != hipSuccess) return e;
         for (int k = 0; k < n_times; ++k)
@@ -443,6 +447,7 @@ struct Plan {
       } else {
         if ((e = launch_walk(wl, st)) != hipSuccess) return e;
       }
+      if (n_merge > 0 && (e = launch_merge_pieces(d_pstat, d_merge, n_merge, d_istat, st)) != hipSuccess) return e;
     }
     if (has_out)
       if ((e = launch_finalize_nodes(d_istat, d_first, n_nodes, d_call, 0, ctr, st)) != hipSuccess) return e;
@@ -558,7 +563,14 @@ struct Items {
   std::vector<WorkItem> q;        // queue order
   std::vector<int64_t> first;     // per node: first slot
   std::vector<int32_t> slot_node; // per slot: node
+  // set by cut_items when items are run in pieces
+  std::vector<MergeJob> merge;
+  int n_pieces = 0;
 };
+
+// Pieces that pdd_mc_interface_noalloc's fixed area takes (48 + 16 + 12 bytes
+// each, with the rest of a call's scratch next to them).
+constexpr int64_t kFixedPieces = 60000;
 
 // Work items, guided sizes.  A node's paths are cut into items of `chunk`
 // paths, except about its last eighth, which is cut into items of chunk / 8
@@ -603,6 +615,32 @@ Items make_items(int64_t n_nodes, const int64_t* counts, int64_t count_all, int 
     return cost[(size_t)a.node] * a.count > cost[(size_t)b.node] * b.count;
   });
   return r;
+}
+
+// Cuts the queued items into pieces of at most `piece` paths, which keep the
+// items' order: q then holds pieces, numbered item by item.  An item's
+// statistics are merged from its pieces' in path order, so the items stay the
+// unit of partials and of resuming.
+void cut_items(int piece, Items* r) {
+  bool any = false;
+  for (const WorkItem& w : r->q) any = any || w.count > (uint32_t)piece;
+  if (!any) return;
+  std::vector<WorkItem> q;
+  q.reserve(r->q.size() * 2);
+  r->merge.reserve(r->q.size());
+  for (const WorkItem& w : r->q) {
+    MergeJob m{w.slot, r->n_pieces, 0};
+    for (uint32_t k = 0; k < w.count; k += (uint32_t)piece) {
+      WorkItem p = w;
+      p.p0 = w.p0 + k;
+      p.count = std::min<uint32_t>((uint32_t)piece, w.count - k);
+      p.slot = r->n_pieces++;
+      q.push_back(p);
+      ++m.count;
+    }
+    r->merge.push_back(m);
+  }
+  r->q.swap(q);
 }
 
 }  // namespace
@@ -910,6 +948,9 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
         if (!o.skip_items[w.slot]) keep.push_back(w);
       items.q.swap(keep);
     }
+    // (the fixed scratch area holds the pieces of small calls only)
+    if (!a.adjoint && (a.fixed == nullptr || total_paths / tune.piece_paths + n_slots <= kFixedPieces))
+      cut_items(tune.piece_paths, &items);
   }
   int n_items = (int)items.q.size();
   pl.n_items = n_items;
@@ -951,6 +992,8 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
     o_items = A.add(sizeof(WorkItem) * std::max(1, n_items));
   }
   o_istat = A.add(sizeof(ItemStat) * std::max<int64_t>(1, n_stat));
+  const size_t o_pstat = A.add(sizeof(ItemStat) * (size_t)items.n_pieces);
+  const size_t o_merge = A.add(sizeof(MergeJob) * items.merge.size());
   o_first = A.add(sizeof(int64_t) * ((size_t)a.n_nodes + 1));
   o_doff = A.add(sizeof(int64_t) * ((size_t)a.n_nodes + 1));
   // adjoint buffers
@@ -1027,6 +1070,7 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
   pl.d_nodes = (double*)(base + o_nodes);
   T.job(StageJob{a.nodes, pl.d_nodes, 0, (int32_t)(a.n_nodes * dim), -1, 0}, -1, 3);
   pl.n_jobs = (int)T.jobs.size();
+  for (const StageJob& j : T.jobs) pl.max_job = std::max(pl.max_job, (int)j.count);
   pl.jobs_host = T.jobs;
   pl.job_src = T.src;
   pl.d_perm = (int32_t*)(base + o_perm);
@@ -1035,6 +1079,9 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
   pl.d_cf = (float*)(base + o_cf);
   pl.d_qhead = (uint32_t*)(base + o_q);
   pl.d_istat = o.partials ? (ItemStat*)o.partials : (ItemStat*)(base + o_istat);
+  pl.d_pstat = items.merge.empty() ? pl.d_istat : (ItemStat*)(base + o_pstat);
+  pl.d_merge = (MergeJob*)(base + o_merge);
+  pl.n_merge = (int)items.merge.size();
   pl.d_first = (int64_t*)(base + o_first);
   int64_t* d_doff = (int64_t*)(base + o_doff);
   pl.has_out = a.out != nullptr;
@@ -1053,6 +1100,7 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
   } else {
     put(ups, o_first, items.first);
     put(ups, o_items, items.q);
+    put(ups, o_merge, items.merge);
   }
   if (a.adjoint) {
     std::vector<double> invn((size_t)std::max<int64_t>(1, a.n_nodes), 0.0);
@@ -1121,13 +1169,16 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
     L.adjoint = a.adjoint;
     L.wos = a.wos;
     L.spec = spec;
-    const int max_blocks = tune.blocks_per_cu * device_cus();
+    // (the forward kernel's wavefronts start on items of their own, so its
+    // grid is what the chip holds at a time)
+    const int held = a.adjoint ? 0 : walk_fwd_blocks(L);
+    const int max_blocks = (held > 0 ? std::min(held, tune.blocks_per_cu) : tune.blocks_per_cu) * device_cus();
     const int need = (n_items + kBlock / kWave - 1) / (kBlock / kWave);
     L.grid = std::max(1, std::min(max_blocks, need));
     L.items = (const WorkItem*)(base + o_items);
     L.n_items = n_items;
     L.qhead = pl.d_qhead;
-    L.istat = pl.d_istat;
+    L.istat = pl.d_pstat;
     L.igrad = pl.d_igrad;
     L.grad_stride = pl.grad_stride;
     L.dump_phi = o.dump_phi;
@@ -1160,6 +1211,52 @@ struct BatchArgs {
   pdd_node_stat* out;
   bool wos;
 };
+
+// Orders a batch's items by problem (each problem's in their queue order).
+// first_wave holds each problem's share of the estimated work in parts of
+// 2^20: paths times steps (est_steps, scaled for boxes, whose paths end at the
+// nearest of 2 d faces; a walk on spheres takes about as many jumps from any
+// node) times the Gaussians of a step.
+std::vector<BatchQueue> order_by_problem(const BatchArgs& a, const std::vector<double>& steps,
+                                         std::vector<WorkItem>* items) {
+  static const double kBoxScale[4] = {1.0, 1.0, 0.6, 0.45};
+  const size_t np = (size_t)a.n_probs;
+  std::vector<size_t> at(np + 1, 0);
+  std::vector<double> work(np, 0.0);
+  double total = 0.0;
+  for (const WorkItem& w : *items) {
+    const size_t k = (size_t)a.node_prob[w.node];
+    const pdd_domain& D = a.probs[k].domain;
+    const double each = a.wos ? 1.0 : steps[(size_t)w.node] * (D.kind == PDD_DOM_BOX ? kBoxScale[D.dim] : 1.0);
+    ++at[k + 1];
+    work[k] += (double)w.count * each * (double)D.dim;
+    total += (double)w.count * each * (double)D.dim;
+  }
+  std::vector<BatchQueue> q(np);
+  for (size_t k = 0; k < np; ++k) {
+    at[k + 1] += at[k];
+    q[k].first_wave = (uint32_t)(total > 0.0 ? work[k] / total * (double)(1 << 20) : 0.0);
+  }
+  std::vector<WorkItem> out(items->size());
+  for (const WorkItem& w : *items) out[at[(size_t)a.node_prob[w.node]]++] = w;
+  items->swap(out);
+  return q;
+}
+
+// Each problem's range of the queue, and the first of the launch's wavefronts
+// that starts on it.
+void place_queues(const BatchArgs& a, const std::vector<WorkItem>& q, int n_waves, std::vector<BatchQueue>* out) {
+  for (const WorkItem& w : q) ++(*out)[(size_t)a.node_prob[w.node]].count;
+  int32_t first = 0;
+  uint64_t before = 0;
+  for (BatchQueue& b : *out) {
+    const uint64_t share = b.first_wave;
+    b.first = first;
+    b.first_wave = (uint32_t)((before * (uint64_t)n_waves) >> 20);
+    first += b.count;
+    before += share;
+  }
+}
 
 pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
   if (a.probs == nullptr) return fail(PDD_ERR_INVALID_ARG, "problems is NULL");
@@ -1265,7 +1362,17 @@ pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
   for (int64_t i = 0; i < a.n_nodes; ++i)
     cost[(size_t)i] = est_steps(a.probs[a.node_prob[i]], &hnodes[(size_t)i * 3], a.dt);
   Items items = make_items(a.n_nodes, a.paths, 0, tune.chunk_paths, cost);
+  const int n_slots = (int)items.q.size();
+  std::vector<BatchQueue> queues = order_by_problem(a, cost, &items.q);
+  cut_items(tune.piece_paths, &items);
   const int n_items = (int)items.q.size();
+  // (wavefronts start on items of their own, so the grid is what the chip
+  // holds at a time)
+  const int held = walk_batch_blocks(fp32, o.rng_layout, a.wos);
+  const int max_blocks = (held > 0 ? std::min(held, tune.blocks_per_cu) : tune.blocks_per_cu) * device_cus();
+  const int need = (n_items + kBlock / kWave - 1) / (kBlock / kWave);
+  const int grid = std::max(1, std::min(max_blocks, need));
+  place_queues(a, items.q, grid * (kBlock / kWave), &queues);
   pl.n_items = n_items;
   pl.n_nodes = a.n_nodes;
   std::vector<int64_t> doff((size_t)a.n_nodes + 1, 0);
@@ -1279,13 +1386,16 @@ pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
   const size_t o_fac = A.add(sizeof(DevFactor) * std::max<size_t>(1, T.fac.size()));
   const size_t o_cd = A.add(sizeof(double) * std::max(1, T.ncoef));
   const size_t o_cf = A.add(sizeof(float) * std::max(1, T.ncoef));
-  const size_t o_q = A.add(sizeof(uint32_t) * 4);
+  pl.n_qhead = kQueueStride * a.n_probs;
+  const size_t o_q = A.add(sizeof(uint32_t) * (size_t)pl.n_qhead);
   const size_t o_items = A.add(sizeof(WorkItem) * std::max(1, n_items));
-  const size_t o_istat = A.add(sizeof(ItemStat) * std::max(1, n_items));
+  const size_t o_istat = A.add(sizeof(ItemStat) * std::max(1, n_slots));
+  const size_t o_pstat = A.add(sizeof(ItemStat) * (size_t)items.n_pieces);
+  const size_t o_merge = A.add(sizeof(MergeJob) * items.merge.size());
   const size_t o_first = A.add(sizeof(int64_t) * ((size_t)a.n_nodes + 1));
   const size_t o_doff = A.add(sizeof(int64_t) * ((size_t)a.n_nodes + 1));
   const size_t o_probs = A.add(sizeof(LinearParams) * (size_t)a.n_probs);
-  const size_t o_nprob = A.add(sizeof(int32_t) * (size_t)a.n_nodes);
+  const size_t o_queues = A.add(sizeof(BatchQueue) * (size_t)a.n_probs);
   ArenaLease lease;
   if (graph) {
     PDD_HIP(hipMalloc(&pl.arena, A.total));
@@ -1299,6 +1409,7 @@ pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
   pl.d_nodes = (double*)(base + o_nodes);
   T.job(StageJob{a.nodes, pl.d_nodes, 0, (int32_t)(a.n_nodes * 3), -1, 0}, -1, 3);
   pl.n_jobs = (int)T.jobs.size();
+  for (const StageJob& j : T.jobs) pl.max_job = std::max(pl.max_job, (int)j.count);
   pl.jobs_host = T.jobs;
   pl.job_src = T.src;
   pl.d_perm = (int32_t*)(base + o_perm);
@@ -1306,6 +1417,9 @@ pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
   pl.d_cf = (float*)(base + o_cf);
   pl.d_qhead = (uint32_t*)(base + o_q);
   pl.d_istat = (ItemStat*)(base + o_istat);
+  pl.d_pstat = items.merge.empty() ? pl.d_istat : (ItemStat*)(base + o_pstat);
+  pl.d_merge = (MergeJob*)(base + o_merge);
+  pl.n_merge = (int)items.merge.size();
   pl.d_first = (int64_t*)(base + o_first);
   pl.has_out = true;
   for (auto& lp : lps) {
@@ -1314,22 +1428,23 @@ pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
     lp.cf = pl.d_cf;
     lp.nodes = pl.d_nodes;
   }
-  std::vector<int32_t> nprob(a.node_prob, a.node_prob + a.n_nodes);
   std::vector<Upload> ups;
   put(ups, o_call, call_block_image(cp, sources(T.jobs, T.src)));
   put(ups, o_perm, T.perm);
   put(ups, o_fac, T.fac);
   put(ups, o_items, items.q);
+  put(ups, o_merge, items.merge);
   put(ups, o_first, items.first);
   put(ups, o_doff, doff);
   put(ups, o_probs, lps);
-  put(ups, o_nprob, nprob);
+  put(ups, o_queues, queues);
   for (const auto& u : ups)
     if (!u.bytes.empty()) PDD_HIP(hipMemcpyAsync(base + u.off, u.bytes.data(), u.bytes.size(), hipMemcpyHostToDevice, st));
 
   WalkBatchLaunch& L = pl.wbl;
   L.probs = (const LinearParams*)(base + o_probs);
-  L.node_prob = (const int32_t*)(base + o_nprob);
+  L.queues = (const BatchQueue*)(base + o_queues);
+  L.n_probs = a.n_probs;
   L.nodes = pl.d_nodes;
   L.fac = (const DevFactor*)(base + o_fac);
   L.cd = pl.d_cd;
@@ -1339,13 +1454,11 @@ pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
   L.fp32 = fp32;
   L.layout = o.rng_layout;
   L.wos = a.wos;
-  const int max_blocks = tune.blocks_per_cu * device_cus();
-  const int need = (n_items + kBlock / kWave - 1) / (kBlock / kWave);
-  L.grid = std::max(1, std::min(max_blocks, need));
+  L.grid = grid;
   L.items = (const WorkItem*)(base + o_items);
   L.n_items = n_items;
   L.qhead = pl.d_qhead;
-  L.istat = pl.d_istat;
+  L.istat = pl.d_pstat;
   L.dump_phi = o.dump_phi;
   L.dump_steps = o.dump_steps;
   L.dump_off = (const int64_t*)(base + o_doff);
@@ -1605,6 +1718,7 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
   pl.d_call = (CallPtrs*)(base + o_call);
   pl.d_jobs = (StageJob*)(base + o_call + kJobsOff);
   pl.n_jobs = (int)T.jobs.size();
+  for (const StageJob& j : T.jobs) pl.max_job = std::max(pl.max_job, (int)j.count);
   pl.d_perm = (int32_t*)(base + o_perm);
   pl.d_cd = (double*)(base + o_cd);
   pl.d_cf = (float*)(base + o_cf);
@@ -1759,6 +1873,7 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   pl.d_call = (CallPtrs*)(base + o_call);
   pl.d_jobs = (StageJob*)(base + o_call + kJobsOff);
   pl.n_jobs = (int)T.jobs.size();
+  for (const StageJob& j : T.jobs) pl.max_job = std::max(pl.max_job, (int)j.count);
   pl.d_perm = (int32_t*)(base + o_perm);
   pl.d_cd = (double*)(base + o_cd);
   pl.d_cf = (float*)(base + o_cf);

@@ -169,41 +169,29 @@ __device__ __forceinline__ void box_muller_d(double ua, double ub, double& z0, d
 
 // The Gaussians of one Philox block.  LIBM: box_muller_libm in FP64.
 template <typename R, int LAYOUT, bool LIBM = false>
-struct Normals;
-
-template <bool LIBM>
-struct Normals<float, RNG_QUAD24, LIBM> {
-  static constexpr int kPerBlock = 4;
-  __device__ __forceinline__ static void gen(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
-                                             uint32_t k1, float* z) {
-    philox4x32_10(c0, c1, c2, c3, k0, k1);
-    box_muller_f(u24f(c0), u24f(c1), z[0], z[1]);
-    box_muller_f(u24f(c2), u24f(c3), z[2], z[3]);
+struct Normals {
+  static constexpr int kPerBlock = LAYOUT == RNG_QUAD24 ? 4 : 2;
+  __device__ __forceinline__ static void pair(R ua, R ub, R* z) {
+    if constexpr (sizeof(R) == 4) box_muller_f(ua, ub, z[0], z[1]);
+    else if constexpr (LIBM) box_muller_libm(ua, ub, z[0], z[1]);
+    else box_muller_d(ua, ub, z[0], z[1]);
   }
-};
-template <bool LIBM>
-struct Normals<double, RNG_QUAD24, LIBM> {
-  static constexpr int kPerBlock = 4;
-  __device__ __forceinline__ static void gen(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
-                                             uint32_t k1, double* z) {
-    philox4x32_10(c0, c1, c2, c3, k0, k1);
-    if constexpr (LIBM) {
-      box_muller_libm(u24d(c0), u24d(c1), z[0], z[1]);
-      box_muller_libm(u24d(c2), u24d(c3), z[2], z[3]);
+  __device__ __forceinline__ static void from_words(const uint32_t* w, R* z) {
+    if constexpr (sizeof(R) == 4) {
+      pair(u24f(w[0]), u24f(w[1]), z);
+      pair(u24f(w[2]), u24f(w[3]), z + 2);
+    } else if constexpr (LAYOUT == RNG_QUAD24) {
+      pair(u24d(w[0]), u24d(w[1]), z);
+      pair(u24d(w[2]), u24d(w[3]), z + 2);
     } else {
-      box_muller_d(u24d(c0), u24d(c1), z[0], z[1]);
-      box_muller_d(u24d(c2), u24d(c3), z[2], z[3]);
+      pair(u52d(w[0], w[1]), u52d(w[2], w[3]), z);
     }
   }
-};
-template <bool LIBM>
-struct Normals<double, RNG_PAIR52, LIBM> {
-  static constexpr int kPerBlock = 2;
   __device__ __forceinline__ static void gen(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0,
-                                             uint32_t k1, double* z) {
-    philox4x32_10(c0, c1, c2, c3, k0, k1);
-    if constexpr (LIBM) box_muller_libm(u52d(c0, c1), u52d(c2, c3), z[0], z[1]);
-    else box_muller_d(u52d(c0, c1), u52d(c2, c3), z[0], z[1]);
+                                             uint32_t k1, R* z) {
+    uint32_t w[4] = {c0, c1, c2, c3};
+    philox4x32_10(w[0], w[1], w[2], w[3], k0, k1);
+    from_words(w, z);
   }
 };
 
@@ -473,6 +461,24 @@ __device__ __forceinline__ Dom<double> make_test_dom<double>(const LinearParams&
   return D;
 }
 
+// |d|^2.  In FP32 the fused products are written out: left to the compiler,
+// which of the first two products is rounded on its own would depend on the
+// code around it, and a path's exit step with it.
+template <typename R, int DIM>
+__device__ __forceinline__ R norm2(const R* d) {
+  if constexpr (sizeof(R) == 4) {
+    if constexpr (DIM == 1) return d[0] * d[0];
+    R s = __builtin_fmaf(d[0], d[0], d[1] * d[1]);
+    if constexpr (DIM == 3) s = __builtin_fmaf(d[2], d[2], s);
+    return s;
+  } else {
+    R s = (R)0;
+#pragma unroll
+    for (int k = 0; k < DIM; ++k) s += d[k] * d[k];
+    return s;
+  }
+}
+
 template <typename R, int DIM>
 __device__ __forceinline__ bool inside(const Dom<R>& D, const R* x) {
   if (D.kind == DOM_BOX) {
@@ -481,13 +487,10 @@ __device__ __forceinline__ bool inside(const Dom<R>& D, const R* x) {
     for (int k = 0; k < DIM; ++k) in = in && (x[k] > D.lo[k]) && (x[k] < D.hi[k]);
     return in;
   }
-  R r2 = (R)0;
+  R d[DIM];
 #pragma unroll
-  for (int k = 0; k < DIM; ++k) {
-    const R d = x[k] - D.ctr[k];
-    r2 += d * d;
-  }
-  return r2 < D.rad2;
+  for (int k = 0; k < DIM; ++k) d[k] = x[k] - D.ctr[k];
+  return norm2<R, DIM>(d) < D.rad2;
 }
 
 // Distance from x to the boundary of D (negative outside): ball R - |x - c|,
@@ -526,13 +529,10 @@ __device__ __forceinline__ R boundary_distance(const Dom<R>& D, const R* x) {
     }
     return m;
   }
-  R r2 = (R)0;
+  R d[DIM];
 #pragma unroll
-  for (int k = 0; k < DIM; ++k) {
-    const R d = x[k] - D.ctr[k];
-    r2 += d * d;
-  }
-  return D.rad - sqrt(r2);
+  for (int k = 0; k < DIM; ++k) d[k] = x[k] - D.ctr[k];
+  return D.rad - sqrt(norm2<R, DIM>(d));
 }
 
 // |z|^2 of one jump's Gaussians (FP64 without fused multiply-add, as above).
@@ -545,10 +545,7 @@ __device__ __forceinline__ R sum_squares(const R* z) {
     for (int k = 0; k < DIM; ++k) s += z[k] * z[k];
     return s;
   }
-  R s = (R)0;
-#pragma unroll
-  for (int k = 0; k < DIM; ++k) s += z[k] * z[k];
-  return s;
+  return norm2<R, DIM>(z);
 }
 
 // x += r z / |z| (z2 = |z|^2): FP64 in the order r (z_k / |z|) with every
@@ -616,13 +613,10 @@ __device__ __forceinline__ void project(const Dom<R>& D, const R* x, R* out) {
       for (int k = 0; k < DIM; ++k) if (k == best) out[k] = target;
     }
   } else {
-    R r2 = (R)0;
+    R d[DIM];
 #pragma unroll
-    for (int k = 0; k < DIM; ++k) {
-      const R d = x[k] - D.ctr[k];
-      r2 += d * d;
-    }
-    const R r = sqrt(r2);
+    for (int k = 0; k < DIM; ++k) d[k] = x[k] - D.ctr[k];
+    const R r = sqrt(norm2<R, DIM>(d));
     if (r == (R)0) {
 #pragma unroll
       for (int k = 0; k < DIM; ++k) out[k] = D.ctr[k] + (k == 0 ? D.rad : (R)0);

@@ -111,10 +111,24 @@ struct WorkItem {
   int32_t slot;
 };
 
+// The queue of one problem of a batch: its items (a range of the batch's item
+// array) and the first wavefront that starts on it.  Queue heads lie
+// kQueueStride words apart, each in a cache line of its own.
+struct BatchQueue {
+  int32_t first, count;
+  uint32_t first_wave, pad;
+};
+constexpr int kQueueStride = 32;
+
 // Partial statistics of one work item (Welford triple + counters).
 struct ItemStat {
   double mean, m2;
   int64_t n, steps, censored, redrawn;
+};
+
+// An item run in pieces: its slot and its pieces' slots.
+struct MergeJob {
+  int32_t item, first, count;
 };
 
 // Copy job of the staging kernel.  With dst == nullptr it fills the staged

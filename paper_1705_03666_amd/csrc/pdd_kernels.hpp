@@ -21,7 +21,7 @@ struct WalkLaunch {
   bool fp32;
   bool adjoint;
   bool wos;                  // walk on spheres (b = c = f = 0; P->dt holds eps)
-  hipFunction_t spec;        // problem-specialised k_walk (runtime-compiled), or null
+  hipFunction_t spec;        // problem-specialised kernel (runtime-compiled), or null
   int grid;
   const WorkItem* items;
   int n_items;
@@ -35,10 +35,11 @@ struct WalkLaunch {
   int refill_groups;
 };
 
-// Heterogeneous batch (walk_batch.hip): per-problem records, node -> problem.
+// Heterogeneous batch (walk_batch.hip): per-problem records and queues.
 struct WalkBatchLaunch {
-  const LinearParams* probs;   // device [n_problems]
-  const int32_t* node_prob;    // device [n_nodes]
+  const LinearParams* probs;   // device [n_probs]
+  const BatchQueue* queues;    // device [n_probs]; queue heads at qhead + k kQueueStride
+  int n_probs;
   const double* nodes;         // device [n_nodes][3]
   const DevFactor* fac;
   const double* cd;
@@ -112,6 +113,10 @@ struct BranchBvpLaunch {
   hipFunction_t spec;        // problem-specialised k_branch_bvp (same arguments), or null
 };
 
+// Blocks of the launch's kernel that a compute unit holds at a time (0 if
+// that cannot be told).
+int walk_fwd_blocks(const WalkLaunch& L);
+int walk_batch_blocks(bool fp32, int layout, bool wos);
 hipError_t launch_walk(const WalkLaunch& L, hipStream_t st);
 hipError_t launch_walk_batch(const WalkBatchLaunch& L, hipStream_t st);
 hipError_t launch_plain(const PlainLaunch& L, hipStream_t st);
@@ -121,6 +126,8 @@ hipError_t launch_branch_bvp(const BranchBvpLaunch& L, hipStream_t st);
 size_t branch_stack_entry_bytes(bool fp32);
 // LDS stack entries per lane of k_branch and k_branch_bvp
 int branch_lds_depth(bool fp32);
+hipError_t launch_merge_pieces(const ItemStat* pstat, const MergeJob* jobs, int n_jobs, ItemStat* istat,
+                               hipStream_t st);
 hipError_t launch_finalize_nodes(const ItemStat* istat, const int64_t* first, int64_t n_nodes, const CallPtrs* cp,
                                  int64_t out_off, unsigned long long* counters, hipStream_t st);
 hipError_t launch_finalize_grad(const double* igrad, int stride, int n_cols, int n_items, const int32_t* slot_node,
@@ -138,9 +145,8 @@ hipError_t launch_node_moments(const void* stats, int64_t n, double* var, double
 hipError_t launch_merge_estimates(void* acc, double* acc_jac, int64_t acc_ld, const void* add, const double* add_jac,
                                   int64_t add_ld, int64_t n_params, const int64_t* index, int64_t n_add,
                                   hipStream_t st);
-hipError_t launch_stage(const StageJob* jobs, int n_jobs, const int32_t* perm, double* cd, float* cf,
-                        hipStream_t st);
-hipError_t launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t st);
+hipError_t launch_stage(const StageJob* jobs, int n_jobs, int max_count, const int32_t* perm, double* cd, float* cf,
+                        uint32_t* qhead, int n_qhead, hipStream_t st);
 hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t st);
 
 }  // namespace pdd

@@ -5,7 +5,7 @@
 // precompiled kernels, for reading and dispatching on every factor record at
 // every step.  Instead the library writes the factor structure of that
 // problem (functions, coordinates, scales, shifts, powers) into C++ source as
-// constants, compiles k_walk with it at run time for the device in use, and
+// constants, compiles the walk with it at run time for the device in use, and
 // launches the result.  Coefficients stay run-time data, so one compiled
 // kernel serves every coefficient value: each thread copies the term
 // coefficients of b, c and f from the staged table into VGPRs once per launch
@@ -34,8 +34,8 @@ namespace pdd {
 // value cannot be written as a literal (non-finite scale or shift).
 std::string spec_terms_source(const LinearParams& P, const std::vector<DevFactor>& fac);
 
-// Loads (compiling on first use, per device) the k_walk instantiation
-// <R, DIM, DFC, LAYOUT, TERMS = true, ADJ, WOS = false, SpecTerms>.  Returns
+// Loads (compiling on first use, per device) the k_walk_fwd or k_walk_adj
+// instantiation for these terms (TERMS = true, policy SpecTerms).  Returns
 // false with a message in *err when the runtime compiler or the module load
 // fails.  Compiled code objects are kept in memory for the life of the
 // process and, when the directory is writable, in $PDD_JIT_CACHE (default

@@ -11,6 +11,7 @@ namespace pdd {
 
 struct Tuning {
   int chunk_paths;
+  int piece_paths;   // forward walks: an item is run in pieces of at most this many paths
   int blocks_per_cu;
   int refill_groups;
 };

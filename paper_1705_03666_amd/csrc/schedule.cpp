@@ -155,6 +155,17 @@ Tuning choose_schedule(int kernel, int dim, int precision, const pdd_options& o,
     while (t.chunk_paths > 1024 && total_work / t.chunk_paths < per_wave * waves) t.chunk_paths /= 2;
   }
   t.chunk_paths = std::max(1, t.chunk_paths);
+  // the forward walks stream from piece to piece without draining, so a small
+  // call's items are cut finer: until every resident wavefront gets four
+  // pieces, down to one path per lane; with fewer paths than lanes, until
+  // every SIMD has a wavefront (whose idle lanes then draw for the others)
+  t.piece_paths = t.chunk_paths;
+  if (kernel == PDD_KERNEL_WALK || kernel == PDD_KERNEL_WOS || kernel == PDD_KERNEL_WALK_BATCH ||
+      kernel == PDD_KERNEL_WOS_BATCH) {
+    const int64_t simds = (int64_t)std::max(1, n_cus) * 4;
+    while (t.piece_paths > 64 && total_work / t.piece_paths < 4 * simds * t.blocks_per_cu) t.piece_paths /= 2;
+    while (t.piece_paths > 4 && total_work / t.piece_paths < simds) t.piece_paths /= 2;
+  }
   return t;
 }
 

@@ -369,12 +369,14 @@ bool load_spec(const std::string& name, const std::string& src, hipFunction_t* f
 
 std::string spec_walk_name(bool fp32, int dim, int dfc, int layout, bool adjoint) {
   std::ostringstream nm;
-  nm << "pdd::k_walk<" << (fp32 ? "float" : "double") << ", " << dim << ", " << dfc << ", " << layout << ", true, "
-     << (adjoint ? "true" : "false") << ", false, pdd_spec::SpecTerms>";
+  nm << "pdd::" << (adjoint ? "k_walk_adj<" : "k_walk_fwd<") << (fp32 ? "float" : "double") << ", " << dim << ", "
+     << dfc << ", " << layout << ", true, " << (adjoint ? "" : "false, ") << "pdd_spec::SpecTerms>";
   return nm.str();
 }
 
-std::string spec_walk_source(const std::string& terms_src) { return "#include \"walk_kernels.hpp\"\n" + terms_src; }
+std::string spec_walk_source(const std::string& terms_src) {
+  return "#include \"walk_kernels.hpp\"\n#include \"walk_stream.hpp\"\n" + terms_src;
+}
 
 bool spec_walk_kernel(const std::string& terms_src, bool fp32, int dim, int dfc, int layout, bool adjoint,
                       hipFunction_t* fn, std::string* err) {

@@ -6,7 +6,7 @@
 namespace pdd {
 
 hipError_t launch_walk_adj_f32(const WalkLaunch& L, hipStream_t st) {
-  return launch_walk_terms<float, RNG_QUAD24, true>(L, st);
+  return launch_adj_terms<float, RNG_QUAD24>(L, st);
 }
 
 }  // namespace pdd

@@ -6,8 +6,8 @@
 namespace pdd {
 
 hipError_t launch_walk_adj_f64(const WalkLaunch& L, hipStream_t st) {
-  if (L.P->layout == RNG_QUAD24) return launch_walk_terms<double, RNG_QUAD24, true>(L, st);
-  return launch_walk_terms<double, RNG_PAIR52, true>(L, st);
+  if (L.P->layout == RNG_QUAD24) return launch_adj_terms<double, RNG_QUAD24>(L, st);
+  return launch_adj_terms<double, RNG_PAIR52>(L, st);
 }
 
 template <int DIM, int DFC, int LAYOUT, int NT>

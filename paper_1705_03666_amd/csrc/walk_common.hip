@@ -2,34 +2,64 @@
 // dispatch of the walk launch to its instantiation unit.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "pdd_device.hpp"
 #include "pdd_kernels.hpp"
 
 namespace pdd {
 
 // ---------------------------------------------------------------------------
-// Merge item partials into per-node statistics in item-slot order (fixed).
-__global__ void k_finalize_nodes(const ItemStat* __restrict__ istat, const int64_t* __restrict__ first,
-                                 int64_t n_nodes, const CallPtrs* __restrict__ cp, int64_t out_off,
-                                 unsigned long long* __restrict__ counters) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_nodes) return;
-  pdd_node_stat_dev* __restrict__ out = (pdd_node_stat_dev*)cp->out + out_off;
+// Statistics of the items of one group (lane l takes entries l, l + 64, ..,
+// then the lanes are merged pairwise: a fixed order), in every lane.
+__device__ __forceinline__ ItemStat merge_group(const ItemStat* __restrict__ s, int64_t count, int lane) {
   double n = 0.0, m = 0.0, q = 0.0;
   int64_t st = 0, ce = 0, rd = 0;
-  for (int64_t s = first[i]; s < first[i + 1]; ++s) {
-    const ItemStat v = istat[s];
+  for (int64_t i = lane; i < count; i += kWave) {
+    const ItemStat v = s[i];
     chan_merge(n, m, q, (double)v.n, v.mean, v.m2);
     st += v.steps;
     ce += v.censored;
     rd += v.redrawn;
   }
+  wave_welford(n, m, q);
+  ItemStat r;
+  r.mean = m;
+  r.m2 = q;
+  r.n = (int64_t)n;
+  r.steps = wave_sum(st);
+  r.censored = wave_sum(ce);
+  r.redrawn = wave_sum(rd);
+  return r;
+}
+
+// Merge the pieces' statistics into their items', one wavefront per item.
+__global__ void k_merge_pieces(const ItemStat* __restrict__ pstat, const MergeJob* __restrict__ jobs, int n_jobs,
+                               ItemStat* __restrict__ istat) {
+  const int lane = (int)(threadIdx.x & (kWave - 1));
+  const int i = (int)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
+  if (i >= n_jobs) return;
+  const MergeJob J = jobs[i];
+  const ItemStat r = merge_group(pstat + J.first, J.count, lane);
+  if (lane == 0) istat[J.item] = r;
+}
+
+// Merge item partials into per-node statistics, one wavefront per node.
+__global__ void k_finalize_nodes(const ItemStat* __restrict__ istat, const int64_t* __restrict__ first,
+                                 int64_t n_nodes, const CallPtrs* __restrict__ cp, int64_t out_off,
+                                 unsigned long long* __restrict__ counters) {
+  const int lane = (int)(threadIdx.x & (kWave - 1));
+  const int64_t i = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+  if (i >= n_nodes) return;
+  const int64_t f = first[i];
+  const ItemStat v = merge_group(istat + f, first[i + 1] - f, lane);
+  if (lane != 0) return;
   pdd_node_stat_dev r;
-  r.mean = m; r.m2 = q; r.n = (int64_t)n; r.steps = st; r.censored = ce;
-  out[i] = r;
-  if (counters != nullptr && (ce != 0 || rd != 0)) {
-    if (ce) atomicAdd(&counters[0], (unsigned long long)ce);
-    if (rd) atomicAdd(&counters[1], (unsigned long long)rd);
+  r.mean = v.mean; r.m2 = v.m2; r.n = v.n; r.steps = v.steps; r.censored = v.censored;
+  ((pdd_node_stat_dev*)cp->out + out_off)[i] = r;
+  if (counters != nullptr) {
+    if (v.censored) atomicAdd(&counters[0], (unsigned long long)v.censored);
+    if (v.redrawn) atomicAdd(&counters[1], (unsigned long long)v.redrawn);
   }
 }
 
@@ -79,21 +109,26 @@ __global__ void k_scatter_add(const double* __restrict__ src, const int32_t* __r
   if (k < count) dst[map ? map[k] : k] += src[k];
 }
 
-// Copy the caller's coefficient arrays into the staged FP64/FP32 tables.
+// Copy the caller's coefficient arrays into the staged FP64/FP32 tables, and
+// clear the queue heads.  blockIdx.x = job, the blocks of one job share its
+// entries (one block for all jobs took 25 us for a batch of 8 problems and
+// 4096 nodes, a serial chain of small loads; 5 us this way).
 __global__ void k_stage(const StageJob* __restrict__ jobs, int n_jobs, const int32_t* __restrict__ perm,
-                        double* __restrict__ cd, float* __restrict__ cf) {
-  for (int j = 0; j < n_jobs; ++j) {
-    const StageJob J = jobs[j];
-    if (J.dst != nullptr) {
-      for (int k = threadIdx.x; k < J.count; k += blockDim.x) J.dst[k] = J.src[k];
-      continue;
-    }
-    for (int k = threadIdx.x; k < J.count; k += blockDim.x) {
-      const int src = J.perm_off >= 0 ? perm[J.perm_off + k] : k;
-      const double v = J.src != nullptr ? J.src[src] : 0.0;
-      cd[J.dst_off + k] = v;
-      cf[J.dst_off + k] = (float)v;
-    }
+                        double* __restrict__ cd, float* __restrict__ cf, uint32_t* __restrict__ qhead, int n_qhead) {
+  const int first = (int)(blockIdx.y * blockDim.x + threadIdx.x), stride = (int)(gridDim.y * blockDim.x);
+  if (blockIdx.x == 0)
+    for (int k = first; k < n_qhead; k += stride) qhead[k] = 0u;
+  if ((int)blockIdx.x >= n_jobs) return;
+  const StageJob J = jobs[blockIdx.x];
+  if (J.dst != nullptr) {
+    for (int k = first; k < J.count; k += stride) J.dst[k] = J.src[k];
+    return;
+  }
+  for (int k = first; k < J.count; k += stride) {
+    const int src = J.perm_off >= 0 ? perm[J.perm_off + k] : k;
+    const double v = J.src != nullptr ? J.src[src] : 0.0;
+    cd[J.dst_off + k] = v;
+    cf[J.dst_off + k] = (float)v;
   }
 }
 
@@ -184,11 +219,6 @@ __global__ void k_node_moments(const pdd_node_stat_dev* __restrict__ stats, int6
   if (se != nullptr) se[i] = s.n > 0 ? sqrt(v / (double)s.n) : 0.0;
 }
 
-__global__ void k_fill_u32(uint32_t* p, int n, uint32_t v) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
 __global__ void k_fill_f64(double* p, int64_t n, double v) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -198,11 +228,10 @@ hipError_t launch_walk_fwd(const WalkLaunch& L, hipStream_t st);
 hipError_t launch_walk_adj_f32(const WalkLaunch& L, hipStream_t st);
 hipError_t launch_walk_adj_f64(const WalkLaunch& L, hipStream_t st);
 
-hipError_t launch_walk_wos(const WalkLaunch& L, hipStream_t st);
-
 hipError_t launch_walk(const WalkLaunch& L, hipStream_t st) {
+  if (!L.adjoint) return launch_walk_fwd(L, st);
   if (L.spec != nullptr) {
-    // same argument list as k_walk; the parameter block is passed by value
+    // same argument list as k_walk_adj; the parameter block is passed by value
     const WorkItem* items = L.items;
     int n_items = L.n_items, grad_stride = L.grad_stride, refill = L.refill_groups;
     uint32_t* qhead = L.qhead;
@@ -215,14 +244,19 @@ hipError_t launch_walk(const WalkLaunch& L, hipStream_t st) {
                     &dump_off, &refill};
     return hipModuleLaunchKernel(L.spec, (unsigned)L.grid, 1, 1, kBlock, 1, 1, 0, st, args, nullptr);
   }
-  if (L.wos) return launch_walk_wos(L, st);
-  if (!L.adjoint) return launch_walk_fwd(L, st);
   return L.fp32 ? launch_walk_adj_f32(L, st) : launch_walk_adj_f64(L, st);
+}
+
+hipError_t launch_merge_pieces(const ItemStat* pstat, const MergeJob* jobs, int n_jobs, ItemStat* istat,
+                               hipStream_t st) {
+  const int blocks = (n_jobs + kBlock / kWave - 1) / (kBlock / kWave);
+  hipLaunchKernelGGL(k_merge_pieces, dim3((unsigned)blocks), dim3(kBlock), 0, st, pstat, jobs, n_jobs, istat);
+  return hipGetLastError();
 }
 
 hipError_t launch_finalize_nodes(const ItemStat* istat, const int64_t* first, int64_t n_nodes, const CallPtrs* cp,
                                  int64_t out_off, unsigned long long* counters, hipStream_t st) {
-  const int64_t blocks = (n_nodes + kBlock - 1) / kBlock;
+  const int64_t blocks = (n_nodes + kBlock / kWave - 1) / (kBlock / kWave);
   hipLaunchKernelGGL(k_finalize_nodes, dim3((unsigned)blocks), dim3(kBlock), 0, st, istat, first, n_nodes, cp,
                      out_off, counters);
   return hipGetLastError();
@@ -273,14 +307,11 @@ hipError_t launch_node_moments(const void* stats, int64_t n, double* var, double
   return hipGetLastError();
 }
 
-hipError_t launch_stage(const StageJob* jobs, int n_jobs, const int32_t* perm, double* cd, float* cf,
-                        hipStream_t st) {
-  hipLaunchKernelGGL(k_stage, dim3(1), dim3(kBlock), 0, st, jobs, n_jobs, perm, cd, cf);
-  return hipGetLastError();
-}
-
-hipError_t launch_fill_u32(uint32_t* p, int n, uint32_t v, hipStream_t st) {
-  hipLaunchKernelGGL(k_fill_u32, dim3((n + kBlock - 1) / kBlock), dim3(kBlock), 0, st, p, n, v);
+hipError_t launch_stage(const StageJob* jobs, int n_jobs, int max_count, const int32_t* perm, double* cd, float* cf,
+                        uint32_t* qhead, int n_qhead, hipStream_t st) {
+  const int share = std::max(1, std::min(16, (max_count + 1023) / 1024));
+  hipLaunchKernelGGL(k_stage, dim3(std::max(1, n_jobs), share), dim3(kBlock), 0, st, jobs, n_jobs, perm, cd, cf, qhead,
+                     n_qhead);
   return hipGetLastError();
 }
 

@@ -1,16 +1,17 @@
 // Feynman-Kac walk kernels (Sec. 2.2, eqs. 2.7-2.9 in the elliptic
 // pure-Dirichlet limit; Euler-Maruyama plus boundary test, Sec. 2.1).
 //
-//  k_walk<R, DIM, DFC, LAYOUT, TERMS, ADJ>  persistent batched kernel: every
-//      wavefront pops work items (node, path range) from a device queue and
-//      runs one path per lane; a lane whose path has exited takes the next
-//      path index of the item ("refill"), so lanes stay busy while exit times
-//      vary tenfold.  R = float: FP32 stepping / transforms; R = double: FP64.
-//      DFC = 3: b, c, f carry a dense cubic part; TERMS: they (or g, for the
-//      adjoint) carry generic terms.  With ADJ the same paths are simulated
-//      with pathwise tangents and the derivative of each path value with
-//      respect to the coefficients of g, f and c is accumulated per item (the
-//      exact derivative of the discrete estimator).
+//  k_walk_adj<R, DIM, DFC, LAYOUT, TERMS>  persistent batched kernel of the
+//      adjoint and of value + Jacobian: every wavefront pops work items (node,
+//      path range) from a device queue and runs one path per lane; a lane
+//      whose path has exited takes the next path index of the item
+//      ("refill"), so lanes stay busy while exit times vary tenfold.  R =
+//      float: FP32 stepping / transforms; R = double: FP64.  DFC = 3: b, c, f
+//      carry a dense cubic part; TERMS: they or g carry generic terms.  The
+//      paths are simulated with pathwise tangents and the derivative of each
+//      path value with respect to the coefficients of g, f and c is
+//      accumulated per item (the exact derivative of the discrete estimator).
+//      (The values alone: k_walk_fwd, walk_stream.hpp.)
 //  k_walk_plain<DIM, DFC, LAYOUT>  the FP64 baseline: one node per launch,
 //      one path per thread until it exits, block-level partial statistics.
 //
@@ -142,7 +143,7 @@ __device__ __forceinline__ const DevFun& fun_of(const LinearParams& P) {
   else return P.g;
 }
 
-// Generic-term evaluation policies of k_walk.  TableTerms interprets the
+// Generic-term evaluation policies of the walks.  TableTerms interprets the
 // staged factor records at run time (any problem).  A problem-specialised
 // policy, generated as source and compiled at run time, has the same members
 // with the factor structure (functions, coordinates, scales, shifts, powers)
@@ -194,15 +195,15 @@ __device__ __forceinline__ R g_value_tp(const LinearParams& P, const typename TP
   return v;
 }
 
-// Persistent batched walk.  Every wavefront pops work items (node, path range)
+// Persistent batched adjoint walk.  Every wavefront pops work items (node, path range)
 // from a device queue and runs one path per lane; a lane whose path has ended
 // takes the next path index of the item, so lanes stay busy while exit times
-// vary tenfold.  Ended paths are parked in LDS as exit records (X, Y, Z and,
-// for the adjoint, the tangent S) and processed 64 at a time, one record per
+// vary tenfold.  Ended paths are parked in LDS as exit records (X, Y, Z and
+// the tangent S) and processed 64 at a time, one record per
 // lane: projection onto the boundary, g, the path value phi = g Y + Z, the
 // FP64 Welford update and the g-part of the derivative.
 //
-// Adjoint (ADJ).  With Z_{n+1} = Z_n + f(X_n) Y_n dt, Y_{n+1} = Y_n
+// With Z_{n+1} = Z_n + f(X_n) Y_n dt, Y_{n+1} = Y_n
 // exp(-c(X_n) dt) and phi = g(X_N) Y_N + Z_N, the exact derivatives of the
 // discrete path value with respect to a coefficient theta_j of f (basis
 // function m_j) and of c are
@@ -226,30 +227,30 @@ __device__ __forceinline__ R g_value_tp(const LinearParams& P, const typename TP
 template <typename R, bool TERMS>
 constexpr int walk_min_waves() { return sizeof(R) == 4 ? (TERMS ? 2 : 4) : 1; }
 
-template <typename R, int DIM, int DFC, int LAYOUT, bool TERMS, bool ADJ, bool WOS = false, class TP = TableTerms>
+template <typename R, int DIM, int DFC, int LAYOUT, bool TERMS, class TP = TableTerms>
 __global__ void __launch_bounds__(kBlock, (walk_min_waves<R, TERMS>()))
-k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, uint32_t* __restrict__ qhead,
-       ItemStat* __restrict__ istat, double* __restrict__ igrad, int grad_stride,
-       double* __restrict__ dump_phi, int64_t* __restrict__ dump_steps, const int64_t* __restrict__ dump_off,
-       int refill_groups) {
-  using NZr = Normals<R, LAYOUT, WOS>;
+k_walk_adj(const LinearParams P, const WorkItem* __restrict__ items, int n_items, uint32_t* __restrict__ qhead,
+           ItemStat* __restrict__ istat, double* __restrict__ igrad, int grad_stride,
+           double* __restrict__ dump_phi, int64_t* __restrict__ dump_steps, const int64_t* __restrict__ dump_off,
+           int refill_groups) {
+  using NZr = Normals<R, LAYOUT>;
   using GS = GroupShape<DIM, NZr::kPerBlock>;
   constexpr int NM = GradedLex<DIM, DFC>::N;
-  constexpr int NT = (ADJ && TERMS) ? kAdjTerms : 0;
-  constexpr int NP = ADJ ? NT + NM : 0;
+  constexpr int NT = TERMS ? kAdjTerms : 0;
+  constexpr int NP = NT + NM;
   constexpr int kRecW = DIM + 2 + NP;
   constexpr int kWaves = kBlock / kWave;
   constexpr int kGMono = GradedLex<DIM, kMaxPolyG>::N;      // g-polynomial monomials, at most
-  constexpr int kCols = ADJ ? 2 * NP + NT + kGMono : 0;
-  constexpr int kSlots = kCols > 0 ? (kCols + kWave - 1) / kWave : 1;
+  constexpr int kCols = 2 * NP + NT + kGMono;
+  constexpr int kSlots = (kCols + kWave - 1) / kWave;
   constexpr int kGSlots = (kGMono + kWave - 1) / kWave;
   // power table of the g-gradient pass, one row of odd stride per record:
   // Y x0^a (a = 0..deg), x1^b, x2^c (b, c = 1..deg), and a constant 1
   constexpr int kPwStride = (DIM * kMaxPolyG + 2) | 1;
   constexpr int kFoldMax = NP > NT ? NP : (NT > 0 ? NT : 1);
   constexpr int kArea0 = kRecW * kWave;
-  constexpr int kArea1 = ADJ ? kWave * kPwStride : 0;
-  constexpr int kArea2 = ADJ ? kWave * (kFoldMax | 1) : 0;
+  constexpr int kArea1 = kWave * kPwStride;
+  constexpr int kArea2 = kWave * (kFoldMax | 1);
   constexpr int kArea = kArea0 > kArea1 ? (kArea0 > kArea2 ? kArea0 : kArea2) : (kArea1 > kArea2 ? kArea1 : kArea2);
 
   const int lane = (int)(threadIdx.x & (kWave - 1));
@@ -261,22 +262,20 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
   __shared__ R area[kWaves][kArea];
   __shared__ uint32_t rec_i[kWaves][2][kWave];   // path, steps | censored << 31
   // FP64 per-item derivative accumulators, column ic at [ic / 64][ic % 64]
-  __shared__ double acc[ADJ ? kWaves : 1][kSlots][kWave];
+  __shared__ double acc[kWaves][kSlots][kWave];
   // g-polynomial monomial k (nested order): its three power-table rows
-  __shared__ uint32_t gmono[ADJ ? kGMono : 1];
-  // The adjoint keeps the statistics of the current item per wavefront in
-  // LDS (FP64 Welford triple (n, mean, M2), step and censoring counts),
-  // merged at every flush, so no lane holds FP64 or 64-bit accumulators
-  // through its register-bound stepping loop; the forward kernels, whose
-  // steps are short, keep them per lane (cheaper flushes).
-  constexpr bool kWaveStats = ADJ;
-  __shared__ double wstat[kWaveStats ? kWaves : 1][3];
-  __shared__ int64_t wcount[kWaveStats ? kWaves : 1][2];
+  __shared__ uint32_t gmono[kGMono];
+  // The statistics of the current item are kept per wavefront in LDS (FP64
+  // Welford triple (n, mean, M2), step and censoring counts), merged at every
+  // flush, so no lane holds FP64 or 64-bit accumulators through the
+  // register-bound stepping loop.
+  __shared__ double wstat[kWaves][3];
+  __shared__ int64_t wcount[kWaves][2];
   R* const rec = &area[wid][0];
   // FP32 walks without generic terms: the dense coefficients of c and f are
   // copied into LDS once per block and read from there at every step (the
   // table-read form makes 40 of the step's FMAs read SGPRs)
-  constexpr bool kLdsPoly = sizeof(R) == 4 && !TERMS && !WOS && DFC >= 0;
+  constexpr bool kLdsPoly = sizeof(R) == 4 && !TERMS && DFC >= 0;
   constexpr int kNMc = GradedLex<DIM, (DFC >= 0 ? DFC : 0)>::N;
   constexpr int kNMp = ((kNMc + 3) / 4) * 4;      // 16-byte aligned rows
   __shared__ __attribute__((aligned(16))) R lpoly[kLdsPoly ? 2 * kNMp : 4];   // row 0: c, row 1: f
@@ -299,8 +298,8 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
   const typename TP::template State<R> tst = TP::template load<R>(P);
   const uint32_t max_steps = (uint32_t)P.max_steps;
   const uint32_t k0 = P.key0, k1 = P.key1;
-  const int ngm = (ADJ && P.g.poly_deg >= 0) ? P.g.n_mono : 0;
-  if constexpr (ADJ) {
+  const int ngm = P.g.poly_deg >= 0 ? P.g.n_mono : 0;
+  {
     if (P.g.poly_deg >= 0 && threadIdx.x == 0) {
       const int deg = P.g.poly_deg, one = DIM * deg + 1;
       int k = 0;
@@ -338,16 +337,12 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
     R Y = (R)1, Z = (R)0;
     uint32_t n = 0;
 
-    double wn = 0.0, wmean = 0.0, wm2 = 0.0;   // per lane (forward kernels)
-    int64_t lsteps = 0, lcens = 0;
-    if constexpr (kWaveStats) {
-      if (lane == 0) {
-        wstat[wid][0] = 0.0;
-        wstat[wid][1] = 0.0;
-        wstat[wid][2] = 0.0;
-        wcount[wid][0] = 0;
-        wcount[wid][1] = 0;
-      }
+    if (lane == 0) {
+      wstat[wid][0] = 0.0;
+      wstat[wid][1] = 0.0;
+      wstat[wid][2] = 0.0;
+      wcount[wid][0] = 0;
+      wcount[wid][1] = 0;
     }
     int nrec = 0;
 
@@ -356,10 +351,8 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
     for (int j = 0; j < NP; ++j) S[j] = Fr[j] = Br[j] = (R)0;
 #pragma unroll
     for (int t = 0; t < NT; ++t) Gr[t] = (R)0;
-    if constexpr (ADJ) {
 #pragma unroll
-      for (int r = 0; r < kSlots; ++r) acc[wid][r][lane] = 0.0;
-    }
+    for (int r = 0; r < kSlots; ++r) acc[wid][r][lane] = 0.0;
 
     // Folds CNT running sums v[] of every lane into accumulator columns
     // ic0.. through an LDS transpose: lane j then adds up column j in FP64.
@@ -402,24 +395,15 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
           const R gv = g_value_tp<R, DIM, TP>(P, tst, xr);
           const R phi = gv * y + z;
           const double ph = (double)phi;
-          if constexpr (kWaveStats) {
-            rph = ph;
-            rsteps = nr & 0x7FFFFFFFu;
-            rcens = nr >> 31;
-          } else {
-            wn += 1.0;
-            const double d1 = ph - wmean;
-            wmean += d1 / wn;
-            wm2 += d1 * (ph - wmean);
-            lsteps += (int64_t)(nr & 0x7FFFFFFFu);
-            lcens += (int64_t)(nr >> 31);
-          }
+          rph = ph;
+          rsteps = nr & 0x7FFFFFFFu;
+          rcens = nr >> 31;
           if (dump_phi != nullptr) {
             const int64_t o = dump_off[node] + (int64_t)pr;
             dump_phi[o] = ph;
             if (dump_steps != nullptr) dump_steps[o] = (int64_t)(nr & 0x7FFFFFFFu);
           }
-          if constexpr (ADJ) {
+          {
 #pragma unroll
             for (int j = 0; j < NP; ++j) Br[j] -= phi * rec[(DIM + 2 + j) * kWave + lane];
 #pragma unroll
@@ -428,7 +412,7 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
             yr = y;
           }
         }
-        if constexpr (kWaveStats) {
+        {
           // the records' values, step and censoring counts into the
           // wavefront's item totals: a butterfly Welford merge over the
           // record lanes, then one Chan merge into the running triple
@@ -446,7 +430,7 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
             wcount[wid][1] += fc;
           }
         }
-        if constexpr (ADJ) {
+        {
           // g polynomial: column k gets the sum over the records of
           // Y monomial_k(X_tau).  Record lanes write their power rows, then
           // lane k % 64 sums monomial k over the records in FP64.
@@ -497,7 +481,7 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
         __builtin_amdgcn_wave_barrier();
         nrec = 0;
       }
-      if constexpr (ADJ) {
+      {
         if constexpr (NP > 0) {
           fold(Fr, NP, 0, (double)dt);
           fold(Br, NP, NP, (double)dt);
@@ -526,37 +510,6 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
         }
 #pragma unroll
         for (int s = 0; s < GS::G; ++s) {
-          if constexpr (WOS) {
-            // walk on spheres: jump by the distance to the boundary in the
-            // direction of this jump's Gaussians, or stop inside the eps
-            // shell.  Predicated, not branched (the branch's exec-mask
-            // bookkeeping is scalar work, and the scalar unit bounds these
-            // short steps): a lane that stops or is inactive jumps by a
-            // radius of 0, an active one by the same operations.
-            const bool act = alive && n < max_steps;
-            const R r = boundary_distance<R, DIM>(D, X);
-            const bool stop = act && !(r >= dt);
-            const bool jump = act && (r >= dt);
-            const R z2 = sum_squares<R, DIM>(&z[s * DIM]);
-            jump_sphere<R, DIM>(X, jump ? r : (R)0, z2, &z[s * DIM]);
-            n += jump ? 1u : 0u;
-            alive = alive && !stop;
-            fin = fin || stop;
-            continue;
-          }
-          if constexpr (DFC < 0 && !TERMS && !ADJ) {
-            // b = c = f = 0 (no polynomial, no terms): the pure-diffusion
-            // step, predicated the same way (an inactive lane adds 0 z)
-            const bool act = alive && n < max_steps;
-            const R m = act ? sdt : (R)0;
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) X[k] = X[k] + m * z[s * DIM + k];
-            n += act ? 1u : 0u;
-            const bool out = act && !inside<R, DIM>(Dt, X);
-            alive = alive && !out;
-            fin = fin || out;
-            continue;
-          }
           if (alive && n < max_steps) {
             R mono[NM > 0 ? NM : 1];
             if constexpr (DFC >= 0) monomials<R, DIM, DFC>(X, mono);
@@ -569,7 +522,7 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
               fv = bcf_value<R, DIM, DFC, TERMS, TP, FUN_F>(P, tst, P.f, X, mono);
               cv = bcf_value<R, DIM, DFC, TERMS, TP, FUN_C>(P, tst, P.c, X, mono);
             }
-            if constexpr (ADJ) {
+            {
 #pragma unroll
               for (int t = 0; t < NT; ++t)
                 if (t < P.f.n_terms) Fr[t] += TP::template term<R, DIM, FUN_F>(P, t, X) * Y;
@@ -583,7 +536,7 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
             // terms known to vanish are skipped: X + 0 dt, Z + 0 and
             // Y exp(0) leave the same bits as evaluating them
             if (P.has_f) Z = Z + fv * Y * dt;
-            if constexpr (ADJ) {
+            {
 #pragma unroll
               for (int t = 0; t < NT; ++t) {
                 if (t < P.c.n_terms) {
@@ -630,8 +583,7 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
       if (alive && n >= max_steps) {
         alive = false;
         fin = true;
-        // walk on spheres: a path already inside the eps shell exits normally
-        cens = WOS ? (boundary_distance<R, DIM>(D, X) >= dt) : true;
+        cens = true;
       }
 
       // ---- park ended paths in LDS, refill their lanes with the item's next paths
@@ -677,28 +629,17 @@ k_walk(const LinearParams P, const WorkItem* __restrict__ items, int n_items, ui
 
     // ---- item results
     flush();
-    if constexpr (kWaveStats) {
-      wn = wstat[wid][0];
-      wmean = wstat[wid][1];
-      wm2 = wstat[wid][2];
-      lsteps = wcount[wid][0];
-      lcens = wcount[wid][1];
-    } else {
-      wave_welford(wn, wmean, wm2);
-      lsteps = wave_sum(lsteps);
-      lcens = wave_sum(lcens);
-    }
     if (lane == 0 && istat != nullptr) {
       ItemStat st;
-      st.mean = wmean;
-      st.m2 = wm2;
-      st.n = (int64_t)wn;
-      st.steps = lsteps;
-      st.censored = lcens;
+      st.mean = wstat[wid][1];
+      st.m2 = wstat[wid][2];
+      st.n = (int64_t)wstat[wid][0];
+      st.steps = wcount[wid][0];
+      st.censored = wcount[wid][1];
       st.redrawn = 0;
       istat[it.slot] = st;
     }
-    if constexpr (ADJ) {
+    {
       // row layout: [g terms NT | g poly nested ngm | f NP | c NP];
       // accumulator column ic: [f NP | c NP | g terms NT | g poly ngm]
       double* row = igrad + (size_t)it.slot * (size_t)grad_stride;
@@ -810,7 +751,7 @@ k_walk_plain(const LinearParams P, int node, uint32_t n_paths, ItemStat* __restr
 //   F_j += m_j Y dt,  A_j += f Y dt S_j (before S moves),  S_j += m_j dt,
 // and at the exit d phi/d f_j = F_j, d phi/d c_j = -g Y S_j - A_j,
 // d phi/d g_k = Y G_k(X_tau).  Each block reduces its paths' derivatives
-// into one row (layout as k_walk: [g terms NT | g poly nested | f NP | c NP])
+// into one row (layout as k_walk_adj: [g terms NT | g poly nested | f NP | c NP])
 // and its statistics into one ItemStat.
 template <int DIM, int DFC, int LAYOUT, int NT>
 __global__ void __launch_bounds__(kBlock)
@@ -963,32 +904,29 @@ k_walk_plain_adj(const LinearParams P, int node, uint32_t n_paths, ItemStat* __r
 
 #ifndef __HIPCC_RTC__
 // ---------------------------------------------------------------------------
-// Launch of one k_walk instantiation, dispatched on dimension and on whether
+// Launch of one k_walk_adj instantiation, dispatched on dimension and on whether
 // b, c, f have a polynomial part.
-template <typename R, int DIM, int DFC, int LAYOUT, bool TERMS, bool ADJ, bool WOS = false>
-static hipError_t launch_walk_t(const WalkLaunch& L, hipStream_t st) {
-  hipLaunchKernelGGL((k_walk<R, DIM, DFC, LAYOUT, TERMS, ADJ, WOS>), dim3(L.grid), dim3(kBlock), 0, st, *L.P, L.items,
+template <typename R, int DIM, int DFC, int LAYOUT, bool TERMS>
+static hipError_t launch_adj_t(const WalkLaunch& L, hipStream_t st) {
+  hipLaunchKernelGGL((k_walk_adj<R, DIM, DFC, LAYOUT, TERMS>), dim3(L.grid), dim3(kBlock), 0, st, *L.P, L.items,
                      L.n_items, L.qhead, L.istat, L.igrad, L.grad_stride, L.dump_phi, L.dump_steps, L.dump_off,
                      L.refill_groups);
   return hipGetLastError();
 }
 
-template <typename R, int LAYOUT, bool TERMS, bool ADJ>
-static hipError_t launch_walk_dim(const WalkLaunch& L, hipStream_t st) {
+template <typename R, int LAYOUT, bool TERMS>
+static hipError_t launch_adj_dim(const WalkLaunch& L, hipStream_t st) {
   const bool poly = L.dfc >= 0;
   switch (L.P->dim) {
-    case 1:
-      return poly ? launch_walk_t<R, 1, 3, LAYOUT, TERMS, ADJ>(L, st) : launch_walk_t<R, 1, -1, LAYOUT, TERMS, ADJ>(L, st);
-    case 2:
-      return poly ? launch_walk_t<R, 2, 3, LAYOUT, TERMS, ADJ>(L, st) : launch_walk_t<R, 2, -1, LAYOUT, TERMS, ADJ>(L, st);
-    default:
-      return poly ? launch_walk_t<R, 3, 3, LAYOUT, TERMS, ADJ>(L, st) : launch_walk_t<R, 3, -1, LAYOUT, TERMS, ADJ>(L, st);
+    case 1: return poly ? launch_adj_t<R, 1, 3, LAYOUT, TERMS>(L, st) : launch_adj_t<R, 1, -1, LAYOUT, TERMS>(L, st);
+    case 2: return poly ? launch_adj_t<R, 2, 3, LAYOUT, TERMS>(L, st) : launch_adj_t<R, 2, -1, LAYOUT, TERMS>(L, st);
+    default: return poly ? launch_adj_t<R, 3, 3, LAYOUT, TERMS>(L, st) : launch_adj_t<R, 3, -1, LAYOUT, TERMS>(L, st);
   }
 }
 
-template <typename R, int LAYOUT, bool ADJ>
-static hipError_t launch_walk_terms(const WalkLaunch& L, hipStream_t st) {
-  return L.terms ? launch_walk_dim<R, LAYOUT, true, ADJ>(L, st) : launch_walk_dim<R, LAYOUT, false, ADJ>(L, st);
+template <typename R, int LAYOUT>
+static hipError_t launch_adj_terms(const WalkLaunch& L, hipStream_t st) {
+  return L.terms ? launch_adj_dim<R, LAYOUT, true>(L, st) : launch_adj_dim<R, LAYOUT, false>(L, st);
 }
 
 #endif  // __HIPCC_RTC__
