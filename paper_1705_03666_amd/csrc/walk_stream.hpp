@@ -407,7 +407,7 @@ __device__ __forceinline__ void stream_walk(const PROB& prob, const StreamArgs& 
   // keep the branches and the waits of a lone wavefront off its steps.
   // (Pure diffusion: V is the position of the running paths, whose mask is
   // `run`, `steps` their steps since n was last brought up to date.)
-  constexpr int kUnit = PROB::kRoll ? 1 : (PROB::kFree ? kFreeUnit : PB);
+  constexpr int kUnit = PROB::kFree ? kFreeUnit : 1;
   auto draw_and_step = [&](auto cap, const PathKey& K, uint32_t blk, int nb, const Ra* zr, int nst, R* V,
                            uint64_t& run, int steps) {
 #pragma unroll 1
@@ -567,8 +567,10 @@ __device__ __forceinline__ void stream_walk(const PROB& prob, const StreamArgs& 
     if (PROB::kRoll || shared) {
       drain(na, am, shared);
     } else {
-      cap = __any(alive && n + span > max_steps);
-      if (cap) window(Yes{});
+      // (steps with drift, killing or a source: one copy, with the cap's test)
+      cap = PROB::kYZ || __any(alive && n + span > max_steps);
+      if (PROB::kYZ) window(Yes{});
+      else if (cap) window(Yes{});
       else window(No{});
     }
     if (cap && alive && n >= max_steps) {
@@ -740,7 +742,7 @@ struct SingleProblem {
 // (pure diffusion, walk on spheres: six waves per SIMD) or 128 (four), those
 // with terms in 256; the FP64 kernels are left unconstrained.
 template <typename R, int DFC, bool TERMS>
-constexpr int fwd_min_waves() { return sizeof(R) == 4 ? (TERMS ? 2 : (DFC < 0 ? 6 : 4)) : 1; }
+constexpr int fwd_min_waves() { return sizeof(R) == 4 ? (TERMS ? 2 : (DFC < 0 ? 6 : 5)) : 1; }
 
 template <typename R, int DIM, int DFC, int LAYOUT, bool TERMS, bool WOS = false, class TP = TableTerms>
 __global__ void __launch_bounds__(kBlock, (fwd_min_waves<R, DFC, TERMS>()))
