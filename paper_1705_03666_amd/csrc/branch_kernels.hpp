@@ -239,9 +239,7 @@ k_branch(const BranchParams P, const WorkItem* __restrict__ items, int n_items, 
   const R Tend = BrScalars<R>::T(P);
   const uint64_t B = (uint64_t)P.label_base;
 
-  for (;;) {
-    const uint32_t it_idx = pop_item(qhead);
-    if (it_idx >= (uint32_t)n_items) break;
+  for (uint32_t it_idx = first_item(); it_idx < (uint32_t)n_items; it_idx = next_item(qhead, n_items)) {
     const WorkItem it = items[it_idx];
     const int point = it.node;
     const uint32_t pend = it.p0 + it.count;
@@ -673,9 +671,7 @@ k_branch_bvp(const BranchParams P, const BranchBoundary BB, const WorkItem* __re
   const uint64_t B = (uint64_t)P.label_base;
   double* const W = &wst[wid][0];
 
-  for (;;) {
-    const uint32_t it_idx = pop_item(qhead);
-    if (it_idx >= (uint32_t)n_items) break;
+  for (uint32_t it_idx = first_item(); it_idx < (uint32_t)n_items; it_idx = next_item(qhead, n_items)) {
     const WorkItem it = items[it_idx];
     const int point = it.node;
     const uint32_t pend = it.p0 + it.count;

@@ -343,6 +343,15 @@ int device_cus() {
   return cus[dev];
 }
 
+// Blocks of a persistent launch: as many per compute unit as asked for, but no
+// more than it holds at a time (`held`, where wavefronts start on items of
+// their own; else 0) and no more than there are items for.
+int persistent_grid(int blocks_per_cu, int held, int n_items) {
+  const int per_cu = held > 0 ? std::min(held, blocks_per_cu) : blocks_per_cu;
+  const int need = (n_items + kBlock / kWave - 1) / (kBlock / kWave);
+  return std::max(1, std::min(per_cu * device_cus(), need));
+}
+
 // per-device warning counters (censored paths, redrawn trees): a device
 // array of the library (zero when the library is loaded), never allocated
 std::mutex g_mu;
@@ -574,17 +583,18 @@ constexpr int64_t kFixedPieces = 60000;
 
 // Work items, guided sizes.  A node's paths are cut into items of `chunk`
 // paths, except about its last eighth, which is cut into items of chunk / 8
-// (at least 256) queued after every large item.  While an item's last paths
+// (at least `least`) queued after every large item.  While an item's last paths
 // finish, the lanes that ran its earlier paths idle; large items make that
 // rare, and the small items at the end of the queue even out the finishing
 // times of the wavefronts.  Slots stay node-major (a node's items are
 // consecutive), so per-node reductions run in a fixed order.  Within each
 // size class the queue is ordered longest first by `cost` when given.
-Items make_items(int64_t n_nodes, const int64_t* counts, int64_t count_all, int chunk, const std::vector<double>& cost) {
+Items make_items(int64_t n_nodes, const int64_t* counts, int64_t count_all, int chunk, const std::vector<double>& cost,
+                 int64_t least = 256) {
   Items r;
   r.first.resize((size_t)n_nodes + 1);
   const int64_t big = std::max(1, chunk);
-  const int64_t small = std::max<int64_t>(std::min<int64_t>(256, big), big / 8);
+  const int64_t small = std::max<int64_t>(std::min<int64_t>(least, big), big / 8);
   std::vector<WorkItem> slots;
   std::vector<char> is_small;
   for (int64_t i = 0; i < n_nodes; ++i) {
@@ -1169,12 +1179,7 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
     L.adjoint = a.adjoint;
     L.wos = a.wos;
     L.spec = spec;
-    // (the forward kernel's wavefronts start on items of their own, so its
-    // grid is what the chip holds at a time)
-    const int held = a.adjoint ? 0 : walk_fwd_blocks(L);
-    const int max_blocks = (held > 0 ? std::min(held, tune.blocks_per_cu) : tune.blocks_per_cu) * device_cus();
-    const int need = (n_items + kBlock / kWave - 1) / (kBlock / kWave);
-    L.grid = std::max(1, std::min(max_blocks, need));
+    L.grid = persistent_grid(tune.blocks_per_cu, a.adjoint ? 0 : walk_fwd_blocks(L), n_items);
     L.items = (const WorkItem*)(base + o_items);
     L.n_items = n_items;
     L.qhead = pl.d_qhead;
@@ -1366,12 +1371,7 @@ pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
   std::vector<BatchQueue> queues = order_by_problem(a, cost, &items.q);
   cut_items(tune.piece_paths, &items);
   const int n_items = (int)items.q.size();
-  // (wavefronts start on items of their own, so the grid is what the chip
-  // holds at a time)
-  const int held = walk_batch_blocks(fp32, o.rng_layout, a.wos);
-  const int max_blocks = (held > 0 ? std::min(held, tune.blocks_per_cu) : tune.blocks_per_cu) * device_cus();
-  const int need = (n_items + kBlock / kWave - 1) / (kBlock / kWave);
-  const int grid = std::max(1, std::min(max_blocks, need));
+  const int grid = persistent_grid(tune.blocks_per_cu, walk_batch_blocks(fp32, o.rng_layout, a.wos), n_items);
   place_queues(a, items.q, grid * (kBlock / kWave), &queues);
   pl.n_items = n_items;
   pl.n_nodes = a.n_nodes;
@@ -1695,9 +1695,12 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
                                       n_points * trees);
   Items items = make_items(n_points, nullptr, trees, tune.chunk_paths, {});
   const int n_items = (int)items.q.size();
-  const int max_blocks = tune.blocks_per_cu * device_cus();
-  const int need = (n_items + kBlock / kWave - 1) / (kBlock / kWave);
-  const int grid = std::max(1, std::min(max_blocks, need));
+  BranchLaunch& BL = pl.bl;
+  BL.P = &pl.bp;
+  BL.fp32 = fp32;
+  BL.layout = o.rng_layout;
+  BL.spec = spec;
+  const int grid = persistent_grid(tune.blocks_per_cu, branch_blocks(BL), n_items);
   const int64_t spill_entries = std::max(0, B.max_segments - branch_lds_depth(fp32));
 
   Arena A;
@@ -1741,10 +1744,6 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
   put(ups, o_items, items.q);
   for (const auto& u : ups)
     if (!u.bytes.empty()) PDD_HIP(hipMemcpyAsync(base + u.off, u.bytes.data(), u.bytes.size(), hipMemcpyHostToDevice, st));
-  BranchLaunch& BL = pl.bl;
-  BL.P = &pl.bp;
-  BL.fp32 = fp32;
-  BL.layout = o.rng_layout;
   BL.grid = grid;
   BL.items = (const WorkItem*)(base + o_items);
   BL.n_items = n_items;
@@ -1755,7 +1754,6 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
   BL.trees = trees;
   BL.stack = base + o_spill;
   BL.stack_entries = spill_entries;
-  BL.spec = spec;
   hipError_t e = pl.enqueue(st);
   (void)lease.done();
   if (e != hipSuccess) return fail(PDD_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
@@ -1848,11 +1846,17 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
 
   const Tuning tune = choose_schedule(PDD_KERNEL_BRANCH_BVP, B.dim, fp32 ? PDD_FP32_STEP : PDD_FP64, o,
                                       device_cus(), n_points * trees);
-  Items items = make_items(n_points, nullptr, trees, tune.chunk_paths, {});
+  // small items down to one tree per lane: a tree takes a thousand sub-steps
+  // or more (795 points x 392 trees, 10 times: 1.96 -> 1.64 ms)
+  Items items = make_items(n_points, nullptr, trees, tune.chunk_paths, {}, kWave);
   const int n_items = (int)items.q.size();
-  const int max_blocks = tune.blocks_per_cu * device_cus();
-  const int need = (n_items + kBlock / kWave - 1) / (kBlock / kWave);
-  const int grid = std::max(1, std::min(max_blocks, need));
+  BranchBvpLaunch& L = pl.bvl;
+  L.P = &pl.bp;
+  L.B = &pl.bb;
+  L.fp32 = fp32;
+  L.layout = o.rng_layout;
+  L.spec = spec;
+  const int grid = persistent_grid(tune.blocks_per_cu, branch_bvp_blocks(L), n_items);
   const int64_t spill_entries = std::max(0, B.max_segments - branch_lds_depth(fp32));
 
   Arena A;
@@ -1897,11 +1901,6 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   put(ups, o_items, items.q);
   for (const auto& u : ups)
     if (!u.bytes.empty()) PDD_HIP(hipMemcpyAsync(base + u.off, u.bytes.data(), u.bytes.size(), hipMemcpyHostToDevice, st));
-  BranchBvpLaunch& L = pl.bvl;
-  L.P = &pl.bp;
-  L.B = &pl.bb;
-  L.fp32 = fp32;
-  L.layout = o.rng_layout;
   L.grid = grid;
   L.items = (const WorkItem*)(base + o_items);
   L.n_items = n_items;
@@ -1912,7 +1911,6 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   L.trees = trees;
   L.stack = base + o_spill;
   L.stack_entries = spill_entries;
-  L.spec = spec;
   hipError_t e = pl.enqueue(st);
   (void)lease.done();
   if (e != hipSuccess) return fail(PDD_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));

@@ -117,6 +117,8 @@ struct BranchBvpLaunch {
 // that cannot be told).
 int walk_fwd_blocks(const WalkLaunch& L);
 int walk_batch_blocks(bool fp32, int layout, bool wos);
+int branch_blocks(const BranchLaunch& L);
+int branch_bvp_blocks(const BranchBvpLaunch& L);
 hipError_t launch_walk(const WalkLaunch& L, hipStream_t st);
 hipError_t launch_walk_batch(const WalkBatchLaunch& L, hipStream_t st);
 hipError_t launch_plain(const PlainLaunch& L, hipStream_t st);
