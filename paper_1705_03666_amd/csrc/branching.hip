@@ -20,19 +20,19 @@ static hipError_t launch_branch_bvp_t(const BranchBvpLaunch& L, hipStream_t st, 
       PDD_BLOCKS((k_branch_bvp<R, 1, LAYOUT>));
       hipLaunchKernelGGL((k_branch_bvp<R, 1, LAYOUT>), dim3(L.grid), dim3(kBlock), 0, st, *L.P, *L.B, L.items,
                          L.n_items, L.qhead, L.istat, L.dump_val, L.dump_segs, L.trees, (StackEntry<R>*)L.stack,
-                         L.stack_entries);
+                         L.stack_entries, L.rings);
       break;
     case 2:
       PDD_BLOCKS((k_branch_bvp<R, 2, LAYOUT>));
       hipLaunchKernelGGL((k_branch_bvp<R, 2, LAYOUT>), dim3(L.grid), dim3(kBlock), 0, st, *L.P, *L.B, L.items,
                          L.n_items, L.qhead, L.istat, L.dump_val, L.dump_segs, L.trees, (StackEntry<R>*)L.stack,
-                         L.stack_entries);
+                         L.stack_entries, L.rings);
       break;
     default:
       PDD_BLOCKS((k_branch_bvp<R, 3, LAYOUT>));
       hipLaunchKernelGGL((k_branch_bvp<R, 3, LAYOUT>), dim3(L.grid), dim3(kBlock), 0, st, *L.P, *L.B, L.items,
                          L.n_items, L.qhead, L.istat, L.dump_val, L.dump_segs, L.trees, (StackEntry<R>*)L.stack,
-                         L.stack_entries);
+                         L.stack_entries, L.rings);
       break;
   }
   return hipGetLastError();
@@ -50,8 +50,9 @@ static hipError_t dispatch_bvp(const BranchBvpLaunch& L, hipStream_t st, int* bl
     int64_t* dump_segs = L.dump_segs;
     int64_t trees = L.trees, stack_entries = L.stack_entries;
     void* stack = L.stack;
+    double* rings = L.rings;
     void* args[] = {(void*)L.P, (void*)L.B, &items, &n_items, &qhead, &istat, &dump_val, &dump_segs,
-                    &trees, &stack, &stack_entries};
+                    &trees, &stack, &stack_entries, &rings};
     return hipModuleLaunchKernel(L.spec, (unsigned)L.grid, 1, 1, kBlock, 1, 1, 0, st, args, nullptr);
   }
   if (L.fp32) return launch_branch_bvp_t<float, RNG_QUAD24>(L, st, blocks);
@@ -91,6 +92,7 @@ int branch_bvp_blocks(const BranchBvpLaunch& L) {
   return dispatch_bvp(L, nullptr, &n) == hipSuccess ? n : 0;
 }
 
+size_t branch_ring_bytes(int n_times) { return sizeof(double) * (size_t)kTreeRing * (size_t)n_times; }
 size_t branch_stack_entry_bytes(bool fp32) { return fp32 ? sizeof(StackEntry<float>) : sizeof(StackEntry<double>); }
 int branch_lds_depth(bool fp32) { return fp32 ? lds_depth<float>() : lds_depth<double>(); }
 

@@ -1846,9 +1846,14 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
 
   const Tuning tune = choose_schedule(PDD_KERNEL_BRANCH_BVP, B.dim, fp32 ? PDD_FP32_STEP : PDD_FP64, o,
                                       device_cus(), n_points * trees);
-  // small items down to one tree per lane: a tree takes a thousand sub-steps
-  // or more (795 points x 392 trees, 10 times: 1.96 -> 1.64 ms)
-  Items items = make_items(n_points, nullptr, trees, tune.chunk_paths, {}, kWave);
+  // Trees stream across a wavefront's items, so short items cost it nothing
+  // and even out the wavefronts' ends: an eighth of a wavefront's share, from
+  // one tree per lane to 256 (1024 points x 10000 trees, 11 times: 33.0 ms
+  // with items of 2048, 28.7 of 512, 26.6 of 256; 27.0 with 64, whose sums
+  // and queue pops show).
+  const int64_t share = n_points * trees / ((int64_t)device_cus() * 128);
+  const int piece = (int)std::min<int64_t>(tune.chunk_paths, std::max<int64_t>(kWave, std::min<int64_t>(256, share)));
+  Items items = make_items(n_points, nullptr, trees, piece, {}, kWave);
   const int n_items = (int)items.q.size();
   BranchBvpLaunch& L = pl.bvl;
   L.P = &pl.bp;
@@ -1871,6 +1876,7 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   const size_t o_first = A.add(sizeof(int64_t) * ((size_t)n_points + 1));
   const size_t o_spill =
       A.add(branch_stack_entry_bytes(fp32) * (size_t)std::max<int64_t>(1, spill_entries) * (size_t)grid * kBlock);
+  const size_t o_rings = A.add(branch_ring_bytes(Bd.n_times) * (size_t)grid * (kBlock / kWave));
   ArenaLease lease;
   PDD_HIP(lease_arena(A.total, st, &lease, &pl.arena));
   char* base = (char*)pl.arena;
@@ -1911,6 +1917,7 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   L.trees = trees;
   L.stack = base + o_spill;
   L.stack_entries = spill_entries;
+  L.rings = (double*)(base + o_rings);
   hipError_t e = pl.enqueue(st);
   (void)lease.done();
   if (e != hipSuccess) return fail(PDD_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));

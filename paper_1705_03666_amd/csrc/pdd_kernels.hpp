@@ -111,6 +111,7 @@ struct BranchBvpLaunch {
   void* stack;
   int64_t stack_entries;
   hipFunction_t spec;        // problem-specialised k_branch_bvp (same arguments), or null
+  double* rings;             // per wavefront branch_ring_bytes(n_times)
 };
 
 // Blocks of the launch's kernel that a compute unit holds at a time (0 if
@@ -126,6 +127,7 @@ hipError_t launch_plain_adj(const PlainLaunch& L, hipStream_t st);
 hipError_t launch_branch(const BranchLaunch& L, hipStream_t st);
 hipError_t launch_branch_bvp(const BranchBvpLaunch& L, hipStream_t st);
 size_t branch_stack_entry_bytes(bool fp32);
+size_t branch_ring_bytes(int n_times);
 // LDS stack entries per lane of k_branch and k_branch_bvp
 int branch_lds_depth(bool fp32);
 hipError_t launch_merge_pieces(const ItemStat* pstat, const MergeJob* jobs, int n_jobs, ItemStat* istat,

@@ -80,3 +80,28 @@ def test_stream_does_not_depend_on_the_cut(precision, wos):
             v = phi[off[i]:off[i + 1]]
             assert g["mean"][i].item() == pytest.approx(v.mean(), rel=1e-13)
             assert g["m2"][i].item() == pytest.approx(np.sum((v - v.mean()) ** 2), rel=1e-9, abs=1e-12)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("trees", [1, 65, 1500])
+def test_branching_trees_stream_independent_of_the_cut(precision, trees):
+    """Trees with a boundary, handed out across items of one tree to more than
+    the ring holds: the same trees bit for bit; the sums are those of the
+    dumped values (the tolerances of the FP64 sums above)."""
+    import paper_1705_03666_amd as pdd
+    from workloads import configs as CF
+    B, Bd = CF.kpp_bvp_travelling_wave(-1.0, 1.5, 0.01, (0.0, 0.25, 0.5, 1.0))
+    pts = np.array([[-0.6], [0.0], [0.8], [1.3], [2.0]])
+    ref = None
+    for kw in ({}, dict(chunk_paths=1, blocks_per_cu=1), dict(chunk_paths=7, blocks_per_cu=1), dict(chunk_paths=700)):
+        print(f"bvp stream {precision} trees={trees} {kw}", flush=True)
+        g = pdd.branching_bvp(B, Bd, pts, trees, 9, precision=precision, dump=True, **kw)
+        torch.cuda.synchronize()
+        ref = g if ref is None else ref
+        assert torch.equal(g["value"], ref["value"]) and torch.equal(g["segments"], ref["segments"])
+        assert torch.equal(g["steps"], ref["steps"]) and torch.equal(g["n"], ref["n"])
+        v = g["value"].double().cpu().numpy()
+        mean = v.mean(axis=1).T
+        assert np.allclose(g["mean"].cpu().numpy(), mean, rtol=1e-12, atol=1e-12)
+        assert np.allclose(g["m2"].cpu().numpy(), ((v - v.mean(axis=1, keepdims=True)) ** 2).sum(axis=1).T,
+                           rtol=1e-9, atol=1e-12)
