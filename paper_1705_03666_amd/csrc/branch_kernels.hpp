@@ -224,7 +224,7 @@ struct StackEntry {
 
 template <typename R, int DIM, int LAYOUT, typename PSI = TablePsi>
 __global__ void __launch_bounds__(kBlock, (branch_min_waves<R>()))
-k_branch(const BranchParams P, const WorkItem* __restrict__ items, int n_items, uint32_t* __restrict__ qhead,
+k_branch(const BranchParams P, const TreeItems items, int n_items, uint32_t* __restrict__ qhead,
          ItemStat* __restrict__ istat, double* __restrict__ dump_val, int64_t* __restrict__ dump_segs,
          int64_t trees, StackEntry<R>* __restrict__ spill, int64_t spill_entries) {
   const int lane = (int)(threadIdx.x & (kWave - 1));
@@ -240,7 +240,7 @@ k_branch(const BranchParams P, const WorkItem* __restrict__ items, int n_items, 
   const uint64_t B = (uint64_t)P.label_base;
 
   for (uint32_t it_idx = first_item(); it_idx < (uint32_t)n_items; it_idx = next_item(qhead, n_items)) {
-    const WorkItem it = items[it_idx];
+    const WorkItem it = items.at(it_idx);
     const int point = it.node;
     const uint32_t pend = it.p0 + it.count;
     R x0[DIM];
@@ -661,7 +661,7 @@ struct OpenTrees {
 
 template <typename R, int DIM, int LAYOUT, typename PSI = TablePsi>
 __global__ void __launch_bounds__(kBlock, (branch_min_waves<R>()))
-k_branch_bvp(const BranchParams P, const BranchBoundary BB, const WorkItem* __restrict__ items, int n_items,
+k_branch_bvp(const BranchParams P, const BranchBoundary BB, const TreeItems items, int n_items,
              uint32_t* __restrict__ qhead, ItemStat* __restrict__ istat, double* __restrict__ dump_val,
              int64_t* __restrict__ dump_segs, int64_t trees, StackEntry<R>* __restrict__ spill,
              int64_t spill_entries, double* __restrict__ rings) {
@@ -800,7 +800,7 @@ k_branch_bvp(const BranchParams P, const BranchBoundary BB, const WorkItem* __re
             more = false;
             return;
           }
-          const WorkItem it = items[it_idx];
+          const WorkItem it = items.at(it_idx);
           it_idx = next_item(qhead, n_items);
           const int node = __builtin_amdgcn_readfirstlane(it.node);
           c_tree = (uint32_t)__builtin_amdgcn_readfirstlane((int)it.p0);

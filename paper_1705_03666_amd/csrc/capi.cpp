@@ -583,18 +583,17 @@ constexpr int64_t kFixedPieces = 60000;
 
 // Work items, guided sizes.  A node's paths are cut into items of `chunk`
 // paths, except about its last eighth, which is cut into items of chunk / 8
-// (at least `least`) queued after every large item.  While an item's last paths
+// (at least 256) queued after every large item.  While an item's last paths
 // finish, the lanes that ran its earlier paths idle; large items make that
 // rare, and the small items at the end of the queue even out the finishing
 // times of the wavefronts.  Slots stay node-major (a node's items are
 // consecutive), so per-node reductions run in a fixed order.  Within each
 // size class the queue is ordered longest first by `cost` when given.
-Items make_items(int64_t n_nodes, const int64_t* counts, int64_t count_all, int chunk, const std::vector<double>& cost,
-                 int64_t least = 256) {
+Items make_items(int64_t n_nodes, const int64_t* counts, int64_t count_all, int chunk, const std::vector<double>& cost) {
   Items r;
   r.first.resize((size_t)n_nodes + 1);
   const int64_t big = std::max(1, chunk);
-  const int64_t small = std::max<int64_t>(std::min<int64_t>(least, big), big / 8);
+  const int64_t small = std::max<int64_t>(std::min<int64_t>(256, big), big / 8);
   std::vector<WorkItem> slots;
   std::vector<char> is_small;
   for (int64_t i = 0; i < n_nodes; ++i) {
@@ -625,6 +624,30 @@ Items make_items(int64_t n_nodes, const int64_t* counts, int64_t count_all, int 
     return cost[(size_t)a.node] * a.count > cost[(size_t)b.node] * b.count;
   });
   return r;
+}
+
+// A branching call's items: about a point's last eighth in items of `small`
+// trees, the rest in items of `big`.
+TreeItems tree_items(int64_t n_points, int64_t trees, int64_t big, int64_t small) {
+  TreeItems t{};
+  t.n_points = (int32_t)n_points;
+  t.trees = (uint32_t)trees;
+  for (;; big *= 2) {
+    small = std::min(small, big);
+    const int64_t n_big = trees > big && small < big ? (trees - trees / 8) / big : 0;
+    const int64_t n_small = (trees - n_big * big + small - 1) / small;
+    if (n_points * (n_big + n_small) > (int64_t)INT32_MAX) continue;   // (slots are 32 bits)
+    t.n_big = (int32_t)n_big;
+    t.n_small = (int32_t)n_small;
+    t.big = (uint32_t)big;
+    t.small = (uint32_t)small;
+    return t;
+  }
+}
+std::vector<int64_t> first_slots(const TreeItems& t) {
+  std::vector<int64_t> first((size_t)t.n_points + 1);
+  for (size_t i = 0; i < first.size(); ++i) first[i] = (int64_t)i * (t.n_big + t.n_small);
+  return first;
 }
 
 // Cuts the queued items into pieces of at most `piece` paths, which keep the
@@ -1693,8 +1716,16 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
   if ((s = branch_spec(o, bp, nullptr, T, fp32, B.dim, false, &spec)) != PDD_OK) return s;
   const Tuning tune = choose_schedule(PDD_KERNEL_BRANCH, B.dim, fp32 ? PDD_FP32_STEP : PDD_FP64, o, device_cus(),
                                       n_points * trees);
-  Items items = make_items(n_points, nullptr, trees, tune.chunk_paths, {});
-  const int n_items = (int)items.q.size();
+  // no longer than a wavefront's share: a call below the schedule's smallest
+  // items, 1024 trees, would leave wavefronts without one (129 points x 3001
+  // trees: 110 us with items of 1024 trees, 85 of 256, 107 of 94 and 127 of 64,
+  // as each item ends with idle lanes and a merge across them; 100 x 7286: 142
+  // with 1024, 97 of 256, 136 of 128)
+  int64_t big = tune.chunk_paths;
+  if (o.chunk_paths == 0)
+    big = std::min(big, std::max<int64_t>(256, n_points * trees / ((int64_t)device_cus() * tune.blocks_per_cu * 4)));
+  const TreeItems items = tree_items(n_points, trees, big, std::max(std::min<int64_t>(256, big), big / 8));
+  const int n_items = items.count();
   BranchLaunch& BL = pl.bl;
   BL.P = &pl.bp;
   BL.fp32 = fp32;
@@ -1710,7 +1741,6 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
   const size_t o_cd = A.add(sizeof(double) * std::max(1, T.ncoef));
   const size_t o_cf = A.add(sizeof(float) * std::max(1, T.ncoef));
   const size_t o_q = A.add(sizeof(uint32_t) * 4);
-  const size_t o_items = A.add(sizeof(WorkItem) * std::max(1, n_items));
   const size_t o_istat = A.add(sizeof(ItemStat) * std::max(1, n_items));
   const size_t o_first = A.add(sizeof(int64_t) * ((size_t)n_points + 1));
   const size_t o_spill =
@@ -1740,12 +1770,11 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
   put(ups, o_call, call_block_image(cpb, T.jobs));
   put(ups, o_perm, T.perm);
   put(ups, o_fac, T.fac);
-  put(ups, o_first, items.first);
-  put(ups, o_items, items.q);
+  put(ups, o_first, first_slots(items));
   for (const auto& u : ups)
     if (!u.bytes.empty()) PDD_HIP(hipMemcpyAsync(base + u.off, u.bytes.data(), u.bytes.size(), hipMemcpyHostToDevice, st));
   BL.grid = grid;
-  BL.items = (const WorkItem*)(base + o_items);
+  BL.items = items;
   BL.n_items = n_items;
   BL.qhead = pl.d_qhead;
   BL.istat = pl.d_istat;
@@ -1846,15 +1875,15 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
 
   const Tuning tune = choose_schedule(PDD_KERNEL_BRANCH_BVP, B.dim, fp32 ? PDD_FP32_STEP : PDD_FP64, o,
                                       device_cus(), n_points * trees);
-  // Trees stream across a wavefront's items, so short items cost it nothing
+  // Trees stream across a wavefront's items, so short items cost it little
   // and even out the wavefronts' ends: an eighth of a wavefront's share, from
   // one tree per lane to 256 (1024 points x 10000 trees, 11 times: 33.0 ms
   // with items of 2048, 28.7 of 512, 26.6 of 256; 27.0 with 64, whose sums
   // and queue pops show).
   const int64_t share = n_points * trees / ((int64_t)device_cus() * 128);
-  const int piece = (int)std::min<int64_t>(tune.chunk_paths, std::max<int64_t>(kWave, std::min<int64_t>(256, share)));
-  Items items = make_items(n_points, nullptr, trees, piece, {}, kWave);
-  const int n_items = (int)items.q.size();
+  const int64_t piece = std::min<int64_t>(tune.chunk_paths, std::max<int64_t>(kWave, std::min<int64_t>(256, share)));
+  const TreeItems items = tree_items(n_points, trees, piece, std::max<int64_t>(kWave, piece / 8));
+  const int n_items = items.count();
   BranchBvpLaunch& L = pl.bvl;
   L.P = &pl.bp;
   L.B = &pl.bb;
@@ -1871,7 +1900,6 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   const size_t o_cd = A.add(sizeof(double) * std::max(1, T.ncoef));
   const size_t o_cf = A.add(sizeof(float) * std::max(1, T.ncoef));
   const size_t o_q = A.add(sizeof(uint32_t) * 4);
-  const size_t o_items = A.add(sizeof(WorkItem) * std::max(1, n_items));
   const size_t o_istat = A.add(sizeof(ItemStat) * (size_t)std::max(1, n_items) * (size_t)Bd.n_times);
   const size_t o_first = A.add(sizeof(int64_t) * ((size_t)n_points + 1));
   const size_t o_spill =
@@ -1903,12 +1931,11 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   put(ups, o_call, call_block_image(cpb, T.jobs));
   put(ups, o_perm, T.perm);
   put(ups, o_fac, T.fac);
-  put(ups, o_first, items.first);
-  put(ups, o_items, items.q);
+  put(ups, o_first, first_slots(items));
   for (const auto& u : ups)
     if (!u.bytes.empty()) PDD_HIP(hipMemcpyAsync(base + u.off, u.bytes.data(), u.bytes.size(), hipMemcpyHostToDevice, st));
   L.grid = grid;
-  L.items = (const WorkItem*)(base + o_items);
+  L.items = items;
   L.n_items = n_items;
   L.qhead = pl.d_qhead;
   L.istat = pl.d_istat;

@@ -111,6 +111,29 @@ struct WorkItem {
   int32_t slot;
 };
 
+// The work items of a branching call, whose points all have the same trees: per
+// point n_big items of `big` trees and then n_small of `small` (the last may be
+// shorter), queued all big ones first.  Worked out where they are needed: a list
+// of 14000 items took the host 0.3 ms to order and copy.
+struct TreeItems {
+  int32_t n_points, n_big, n_small;
+  uint32_t big, small, trees;
+  __host__ __device__ int count() const { return n_points * (n_big + n_small); }
+  __host__ __device__ WorkItem at(uint32_t i) const {
+    const uint32_t n1 = (uint32_t)n_points * (uint32_t)n_big;
+    const bool is_big = i < n1;
+    const uint32_t j = is_big ? i : i - n1, per = (uint32_t)(is_big ? n_big : n_small);
+    const uint32_t node = j / per, k = j - node * per;
+    WorkItem w;
+    w.node = (int32_t)node;
+    w.p0 = is_big ? k * big : (uint32_t)n_big * big + k * small;
+    const uint32_t left = trees - w.p0, most = is_big ? big : small;
+    w.count = left < most ? left : most;
+    w.slot = (int32_t)(node * (uint32_t)(n_big + n_small) + (is_big ? k : (uint32_t)n_big + k));
+    return w;
+  }
+};
+
 // The queue of one problem of a batch: its items (a range of the batch's item
 // array) and the first wavefront that starts on it.  Queue heads lie
 // kQueueStride words apart, each in a cache line of its own.

@@ -81,7 +81,7 @@ struct BranchLaunch {
   bool fp32;
   int layout;
   int grid;
-  const WorkItem* items;
+  TreeItems items;
   int n_items;
   uint32_t* qhead;
   ItemStat* istat;
@@ -101,7 +101,7 @@ struct BranchBvpLaunch {
   bool fp32;
   int layout;
   int grid;
-  const WorkItem* items;
+  TreeItems items;
   int n_items;
   uint32_t* qhead;
   ItemStat* istat;
@@ -111,7 +111,7 @@ struct BranchBvpLaunch {
   void* stack;
   int64_t stack_entries;
   hipFunction_t spec;        // problem-specialised k_branch_bvp (same arguments), or null
-  double* rings;             // per wavefront branch_ring_bytes(n_times)
+  double* rings;             // branch_ring_bytes(n_times) per wavefront
 };
 
 // Blocks of the launch's kernel that a compute unit holds at a time (0 if
