@@ -169,9 +169,12 @@ bool spec_compile(const std::string& src, const std::string& name, const std::st
 std::string spec_terms_source(const LinearParams& P, const std::vector<DevFactor>& fac) {
   std::ostringstream term, sum, load;
   bool first = true;
+  int has_terms = 0, has_poly = 0;   // a bit per function
   int nst = 0;   // state slots: the term coefficients of b, c and f
   for (int w = 0; w < 6; ++w) {
     const DevFun& F = fun_at(P, w);
+    has_terms |= F.n_terms > 0 ? 1 << w : 0;
+    has_poly |= F.poly_deg >= 0 ? 1 << w : 0;
     if (F.n_terms <= 0) continue;
     const char* el = first ? "" : "else ";
     first = false;
@@ -203,6 +206,17 @@ std::string spec_terms_source(const LinearParams& P, const std::vector<DevFactor
   std::ostringstream o;
   o << "namespace pdd_spec {\n"
        "struct SpecTerms {\n"
+       "  static constexpr int kKind = "
+    << P.dom_kind
+    << ";\n"
+       "  template <int W>\n"
+       "  __device__ static __forceinline__ bool has_terms(const pdd::DevFun&) { return ("
+    << has_terms
+    << " >> W) & 1; }\n"
+       "  template <int W>\n"
+       "  __device__ static __forceinline__ bool has_poly(const pdd::DevFun&) { return ("
+    << has_poly
+    << " >> W) & 1; }\n"
        "  template <typename R>\n"
        "  struct State {\n"
        "    R c["

@@ -766,7 +766,8 @@ k_walk_fwd(const LinearParams P, const StreamArgs A) {
   const uint32_t wave = blockIdx.x * kWaves + (uint32_t)__builtin_amdgcn_readfirstlane(wid);
   const uint32_t n_waves = gridDim.x * kWaves;
   if constexpr (Any::kYZ) {
-    stream_walk<R, DIM, LAYOUT>(Any(P, lpoly), A, &lds[wid], lane, wave, n_waves);
+    stream_walk<R, DIM, LAYOUT>(
+        SingleProblem<R, DIM, DFC, TERMS, WOS, TP, TP::kKind>(P, lpoly), A, &lds[wid], lane, wave, n_waves);
   } else if (P.dom_kind == DOM_BOX) {
     stream_walk<R, DIM, LAYOUT>(SingleProblem<R, DIM, DFC, TERMS, WOS, TP, DOM_BOX>(P, lpoly), A, &lds[wid], lane,
                                 wave, n_waves);
