@@ -367,6 +367,69 @@ __device__ __forceinline__ R poly_nested(const double* __restrict__ cd, const fl
   return s;
 }
 
+// s + the N coefficients from idx on times xp, xp x, xp x^2, ..
+template <typename R, int N>
+__device__ __forceinline__ R poly_row(const double* __restrict__ cd, const float* __restrict__ cf, int idx, R s, R xp,
+                                      R x) {
+  R c[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) c[k] = coef_at<R>(cd, cf, idx + k);
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    s += c[k] * xp;
+    xp *= x;
+  }
+  return s;
+}
+
+// poly_nested with straight code for each length of a row of the innermost
+// variable, its coefficients read together, in place of a load, a wait and a
+// branch for each (the same operations in the same order).  For the forward
+// walks: 4096 nodes x 10000 paths on a ball, g of 120 monomials, 25.3 -> 24.5
+// ms; the adjoint walk lost 1 to 2% with it (84.5 -> 85.2 ms at 4096 x 20000).
+template <typename R, int DIM>
+__device__ __forceinline__ R poly_rows(const double* __restrict__ cd, const float* __restrict__ cf, int deg,
+                                         int off, const R* x) {
+  R s = (R)0;
+  int idx = off;
+  auto row = [&](int n, R xp) {
+    switch (n) {
+      case 1: s = poly_row<R, 1>(cd, cf, idx, s, xp, x[DIM - 1]); break;
+      case 2: s = poly_row<R, 2>(cd, cf, idx, s, xp, x[DIM - 1]); break;
+      case 3: s = poly_row<R, 3>(cd, cf, idx, s, xp, x[DIM - 1]); break;
+      case 4: s = poly_row<R, 4>(cd, cf, idx, s, xp, x[DIM - 1]); break;
+      case 5: s = poly_row<R, 5>(cd, cf, idx, s, xp, x[DIM - 1]); break;
+      case 6: s = poly_row<R, 6>(cd, cf, idx, s, xp, x[DIM - 1]); break;
+      case 7: s = poly_row<R, 7>(cd, cf, idx, s, xp, x[DIM - 1]); break;
+      case 8: s = poly_row<R, 8>(cd, cf, idx, s, xp, x[DIM - 1]); break;
+      default:
+        for (int k = 0; k < n; ++k) {
+          s += coef_at<R>(cd, cf, idx + k) * xp;
+          xp *= x[DIM - 1];
+        }
+    }
+    idx += n;
+  };
+  if constexpr (DIM == 1) {
+    row(deg + 1, (R)1);
+  } else {
+    R xa = (R)1;
+    for (int a = 0; a <= deg; ++a) {
+      if constexpr (DIM == 2) {
+        row(deg - a + 1, xa);
+      } else {
+        R xb = xa;
+        for (int b = 0; b <= deg - a; ++b) {
+          row(deg - a - b + 1, xb);
+          xb *= x[1];
+        }
+      }
+      xa *= x[0];
+    }
+  }
+  return s;
+}
+
 // Graded-lexicographic monomial table of total degree <= D in DIM variables,
 // built at compile time so that fully unrolled loops index registers only.
 constexpr int binom(int n, int k) {

@@ -115,7 +115,7 @@ struct BatchProblem {
     g.pad = 0;
     R v = (R)0;
     if (g.n_terms > 0) v = terms_sum<R, DIM>(fac, cd, cf, g, x);
-    if (g.poly_deg >= 0) v += poly_nested<R, DIM>(cd, cf, g.poly_deg, g.poly_off, x);
+    if (g.poly_deg >= 0) v += poly_rows<R, DIM>(cd, cf, g.poly_deg, g.poly_off, x);
     return v;
   }
   __device__ __forceinline__ void step(R* X, R& Y, R& Z, const R* z) const {

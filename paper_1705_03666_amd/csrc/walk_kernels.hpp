@@ -196,12 +196,14 @@ __device__ __forceinline__ R bcf_value(const LinearParams& P, const typename TP:
 }
 
 // g at the projected exit point: generic terms plus the nested polynomial.
-template <typename R, int DIM, class TP>
+template <typename R, int DIM, class TP, bool ROWS = false>
 __device__ __forceinline__ R g_value_tp(const LinearParams& P, const typename TP::template State<R>& st,
                                         const R* xp) {
   R v = (R)0;
   if (TP::template has_terms<FUN_G>(P.g)) v = TP::template sum<R, DIM, FUN_G>(P, st, xp);
-  if (TP::template has_poly<FUN_G>(P.g)) v += poly_nested<R, DIM>(P.cd, P.cf, P.g.poly_deg, P.g.poly_off, xp);
+  if (TP::template has_poly<FUN_G>(P.g))
+    v += ROWS ? poly_rows<R, DIM>(P.cd, P.cf, P.g.poly_deg, P.g.poly_off, xp)
+              : poly_nested<R, DIM>(P.cd, P.cf, P.g.poly_deg, P.g.poly_off, xp);
   return v;
 }
 

@@ -703,7 +703,7 @@ struct SingleProblem {
     d.kind = KIND;
     return boundary_distance<R, DIM>(d, x);
   }
-  __device__ __forceinline__ R g(const R* x) const { return g_value_tp<R, DIM, TP>(P, tst, x); }
+  __device__ __forceinline__ R g(const R* x) const { return g_value_tp<R, DIM, TP, true>(P, tst, x); }
   __device__ __forceinline__ void step(R* X, R& Y, R& Z, const R* z) const {
     R mono[NM > 0 ? NM : 1];
     if constexpr (DFC >= 0) monomials<R, DIM, DFC>(X, mono);

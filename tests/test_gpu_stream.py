@@ -105,3 +105,27 @@ def test_branching_trees_stream_independent_of_the_cut(precision, trees):
         assert np.allclose(g["mean"].cpu().numpy(), mean, rtol=1e-12, atol=1e-12)
         assert np.allclose(g["m2"].cpu().numpy(), ((v - v.mean(axis=1, keepdims=True)) ** 2).sum(axis=1).T,
                            rtol=1e-9, atol=1e-12)
+
+
+@pytest.mark.parametrize("dim", [1, 2, 3])
+@pytest.mark.parametrize("deg", range(9))
+def test_boundary_polynomials_of_every_degree(orc, dim, deg):
+    """Rows of 1 to 9 coefficients, alone and in a batch, per path to 1e-12 of
+    the oracle and bit for bit the same in both."""
+    import paper_1705_03666_amd as pdd
+    from math import comb
+    rng = np.random.default_rng(10 * dim + deg)
+    z = [zero_fun()] * dim
+    P = LinearProblem(ball(dim, 1.0, (0.1,) * dim), 1.0, z, zero_fun(), zero_fun(),
+                      make_fun([], deg, list(rng.standard_normal(comb(dim + deg, dim)))))
+    nodes, paths = np.full((2, dim), 0.2), np.array([65, 30], np.int64)
+    print(f"boundary polynomial dim={dim} deg={deg}", flush=True)
+    o = orc.walk(P, nodes, paths, 4e-3, 5, layout=orc.QUAD24, dump=True)
+    g = pdd.mc_interface(P, nodes, paths, 4e-3, 5, precision="fp64", layout="quad24", dump=True)
+    pad = np.concatenate([nodes, np.zeros((2, 3 - dim))], axis=1)
+    b = pdd.mc_interface_batch([P], np.zeros(2, np.int32), pad, paths, 4e-3, 5, precision="fp64", layout="quad24",
+                               dump=True)
+    torch.cuda.synchronize()
+    phi = np.asarray(o["phi"])
+    assert np.all(np.abs(g["phi"].cpu().numpy() - phi) <= 1e-12 * np.maximum(1.0, np.abs(phi)))
+    assert torch.equal(g["phi"], b["phi"])
