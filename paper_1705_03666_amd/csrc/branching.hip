@@ -42,7 +42,7 @@ static hipError_t dispatch_bvp(const BranchBvpLaunch& L, hipStream_t st, int* bl
   if (L.spec != nullptr) {
     if (blocks != nullptr) return hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(blocks, L.spec, kBlock, 0);
     // same argument list as k_branch_bvp; the parameter blocks are passed by value
-    TreeItems items = L.items;
+    const TreeItems* items = L.items;
     int n_items = L.n_items;
     uint32_t* qhead = L.qhead;
     ItemStat* istat = L.istat;
@@ -100,7 +100,7 @@ static hipError_t dispatch_branch(const BranchLaunch& L, hipStream_t st, int* bl
   if (L.spec != nullptr) {
     if (blocks != nullptr) return hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(blocks, L.spec, kBlock, 0);
     // same argument list as k_branch; the parameter block is passed by value
-    TreeItems items = L.items;
+    const TreeItems* items = L.items;
     int n_items = L.n_items;
     uint32_t* qhead = L.qhead;
     ItemStat* istat = L.istat;

@@ -1748,6 +1748,7 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
   const size_t o_cf = A.add(sizeof(float) * std::max(1, T.ncoef));
   const size_t o_q = A.add(sizeof(uint32_t) * 4);
   const size_t o_istat = A.add(sizeof(ItemStat) * std::max(1, n_items));
+  const size_t o_items = U.add(sizeof(TreeItems));
   const size_t o_first = U.add(sizeof(int64_t) * ((size_t)n_points + 1));
   const size_t o_spill =
       A.add(branch_stack_entry_bytes(fp32) * (size_t)std::max<int64_t>(1, spill_entries) * (size_t)grid * kBlock);
@@ -1779,9 +1780,10 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
   put(&image, o_perm, T.perm);
   put(&image, o_fac, T.fac);
   put(&image, o_first, first_slots(items));
+  put(&image, o_items, std::vector<TreeItems>{items});
   PDD_HIP(hipMemcpyAsync(base, image.data(), image.size(), hipMemcpyHostToDevice, st));
   BL.grid = grid;
-  BL.items = items;
+  BL.items = (const TreeItems*)(base + o_items);
   BL.n_items = n_items;
   BL.qhead = pl.d_qhead;
   BL.istat = pl.d_istat;
@@ -1908,6 +1910,7 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   const size_t o_cf = A.add(sizeof(float) * std::max(1, T.ncoef));
   const size_t o_q = A.add(sizeof(uint32_t) * 4);
   const size_t o_istat = A.add(sizeof(ItemStat) * (size_t)std::max(1, n_items) * (size_t)Bd.n_times);
+  const size_t o_items = U.add(sizeof(TreeItems));
   const size_t o_first = U.add(sizeof(int64_t) * ((size_t)n_points + 1));
   const size_t o_spill =
       A.add(branch_stack_entry_bytes(fp32) * (size_t)std::max<int64_t>(1, spill_entries) * (size_t)grid * kBlock);
@@ -1941,9 +1944,10 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   put(&image, o_perm, T.perm);
   put(&image, o_fac, T.fac);
   put(&image, o_first, first_slots(items));
+  put(&image, o_items, std::vector<TreeItems>{items});
   PDD_HIP(hipMemcpyAsync(base, image.data(), image.size(), hipMemcpyHostToDevice, st));
   L.grid = grid;
-  L.items = items;
+  L.items = (const TreeItems*)(base + o_items);
   L.n_items = n_items;
   L.qhead = pl.d_qhead;
   L.istat = pl.d_istat;

@@ -81,7 +81,7 @@ struct BranchLaunch {
   bool fp32;
   int layout;
   int grid;
-  TreeItems items;
+  const TreeItems* items;
   int n_items;
   uint32_t* qhead;
   ItemStat* istat;
@@ -101,7 +101,7 @@ struct BranchBvpLaunch {
   bool fp32;
   int layout;
   int grid;
-  TreeItems items;
+  const TreeItems* items;
   int n_items;
   uint32_t* qhead;
   ItemStat* istat;
