@@ -70,9 +70,9 @@ OPS_PER_PS_ADJ_SURVEY = 230.0
 # kernel sources and the schedule they were counted on: otherwise the bench
 # reports null.
 TRAFFIC_SOURCES = ['paper_1705_03666_amd/csrc/walk_kernels.hpp', 'paper_1705_03666_amd/csrc/pdd_device.hpp', 'paper_1705_03666_amd/csrc/pdd_internal.hpp', 'paper_1705_03666_amd/csrc/walk_adj_f32.hip']
-TRAFFIC_SHA256 = "2be92012d1389510fa494e35ddad7e11c09923fcce68f3ddbc21ac6344958726"
+TRAFFIC_SHA256 = "59a57c0d54e1b401de94751d785d7c49a6b58dc43cfd8e558c61eecff710edf6"
 TRAFFIC_SCHEDULE = {"chunk_paths": 32768, "blocks_per_cu": 8, "refill_groups": 3}
-TRAFFIC_BYTES = 60.83e6 + 238.86e6
+TRAFFIC_BYTES = 60.34e6 + 238.94e6
 
 
 def traffic_bytes(schedule=None):
@@ -383,7 +383,7 @@ def run(args):
         "speedup_vs_plain_fp64_at_se_1e-3": nodes_per_s / plain_nodes_per_s,
         "mean_steps_per_path": float(mean_steps.mean().item()),
         "gpu_clock_during_steps": sclk,
-        "roofline": {"bound": "alu", "kernel": f"k_walk ({dominant}, FP32, DIM 3)", "achieved": achieved,
+        "roofline": {"bound": "alu", "kernel": f"k_walk_{'adj' if dominant == 'adjoint' else 'fwd'} ({dominant}, FP32, DIM 3)", "achieved": achieved,
                      "peak": peak, "unit": "Top/s", "frac": achieved / peak, "traffic": traffic_bytes(sched_a),
                      "ops_per_path_step": OPS_PER_PS_ADJ if dominant == "adjoint" else OPS_PER_PS_FWD,
                      "ops_per_path_step_survey_unit": OPS_PER_PS_ADJ_SURVEY,

@@ -448,9 +448,8 @@ k_branch(const BranchParams P, const TreeItems* __restrict__ items, int n_items,
 // particle found outside is projected and stopped: every output time t_i >= s picks up g(P X, t_i - s).
 // A particle inside at an output time t_k multiplies factor k by psi(X); a
 // branching at time s multiplies every factor with t_i > s by alpha_I / q_I.
-// The per-tree factors are FP64 products; a finished tree enters the
-// wavefront's FP64 Welford triple of every output time (kept in LDS, lanes
-// in order).  Lanes run sub-steps in rounds over windows of their Gaussians
+// The per-tree factors are FP64 products; a finished tree's go to a ring, from
+// which the sums of every output time are formed in tree order.  Lanes run sub-steps in rounds over windows of their Gaussians
 // (bvp_round) and stop at their first event (output time, stop, death, end),
 // which is handled after the round, so the rare event code is not
 // interleaved with every sub-step.

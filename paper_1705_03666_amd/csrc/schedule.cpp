@@ -111,10 +111,10 @@ bool lookup(int kernel, int dim, int precision, Entry* out) {
 // (k_branch_bvp), 1024 points x 1e5 trees, for branching: four blocks per
 // CU (the FP32 branching kernels are built for four waves per SIMD, and
 // their LDS stacks allow four blocks), items of 16384 trees for k_branch
-// (C4: 3.36 ms against 3.60 with 8192 and 4.77 with 32768; 2 blocks and
-// 2048-tree items took 2.0x) and of 8192 trees for k_branch_bvp, whose trees
-// are long enough that the last items of a launch decide its end (C6: 233.5
-// ms against 238.1 with 4096).
+// (C4: 3.36 ms against 3.60 with 8192 and 4.77 with 32768, measured when it
+// took 3.36; 2 blocks and 2048-tree items took 2.0x) and of at most 8192 trees
+// for k_branch_bvp, whose trees stream across items (run_branching_bvp cuts
+// them to 256 or less).
 Entry defaults(int kernel, bool fp32, int dim) {
   (void)dim;
   if (kernel == PDD_KERNEL_BRANCH) return Entry{16384, fp32 ? 4 : 2, 1};
