@@ -636,7 +636,7 @@ TreeItems tree_items(int64_t n_points, int64_t trees, int64_t big, int64_t small
   TreeItems t{};
   t.n_points = (int32_t)n_points;
   t.trees = (uint32_t)trees;
-  for (;; big *= 2) {
+  for (;; big *= 2, small *= 2) {
     small = std::min(small, big);
     const int64_t n_big = trees > big && small < big ? (trees - trees / 8) / big : 0;
     const int64_t n_small = (trees - n_big * big + small - 1) / small;
