@@ -221,7 +221,10 @@ typedef struct {
   int32_t schedule;       /* pdd_schedule */
   int32_t chunk_paths;    /* paths per large work item (about the last eighth of each node's paths
                              goes into items of chunk_paths/8, at least 256, queued last);
-                             0 = the schedule table (tuned entry, else default) */
+                             0 = the schedule table (tuned entry, else default), made smaller for
+                             a small call; pdd_branching_bvp then takes a tuned entry, or 256 trees,
+                             as the size where a wavefront gets at most 32 such items, and a larger
+                             one for a larger call (an item keeps 48 bytes per output time) */
   int32_t blocks_per_cu;  /* persistent grid size per compute unit; 0 = the schedule table */
   int32_t refill_groups;  /* step groups between lane refills; 0 = the schedule table */
   int32_t boundary_correction; /* linear walks: 0 = plain exit test (X outside D after a step);
@@ -483,7 +486,8 @@ int64_t pdd_item_count(int32_t kernel, int32_t dim, int64_t n_nodes, const int64
  *    process's table; 1 <= chunk_paths <= 2^30, 1 <= blocks_per_cu,
  *    refill_groups <= 64, else PDD_ERR_INVALID_ARG.
  *  pdd_get_schedule: the entry a call would start from (tuned, or the
- *    default), *tuned = 1 if it is a table entry.
+ *    default; the item size of pdd_branching_bvp's default is not used, see
+ *    chunk_paths), *tuned = 1 if it is a table entry.
  *  pdd_save_schedules / pdd_load_schedules: write the table to / merge a file
  *    into it (path NULL = the default file); PDD_ERR_INVALID_ARG if the file
  *    cannot be written / read. */

@@ -32,6 +32,14 @@ BRANCH_SPACE = {
     "chunk_paths": [2048, 4096, 8192, 12288, 14336, 16384, 24576, 32768],
     "blocks_per_cu": [2, 3, 4, 6, 8],
 }
+# with a boundary the trees stream across items, and items of 256 trees are
+# the untuned choice: 1024 points x 10000 trees, 11 times, took 26.6 ms with
+# them, 28.7 with 512 and 33.0 with 2048
+BVP_ITEM = 256
+BVP_SPACE = {
+    "chunk_paths": [128, 256, 512, 1024, 2048, 4096, 8192],
+    "blocks_per_cu": [2, 3, 4, 6, 8],
+}
 
 
 def items_per_node(paths: int, chunk: int) -> int:
@@ -175,7 +183,9 @@ def tune_branching(problem, points, trees: int, seed: int = 0, precision: str = 
     library's table.  The sample gives every resident wavefront at least
     `items_per_wave` items, so it sees the imbalance at the end of a launch
     that the caller's workload will see (with 1024 points x 1e5 trees it is
-    the whole workload)."""
+    the whole workload).  With a boundary every candidate runs the sample of
+    the longest items: short items of a small sample would show the drain of
+    the wavefronts instead of their own cost."""
     kernel = "branch_bvp" if boundary is not None else "branch"
     dim = int(problem.ndim)
     s = _start(kernel, dim, precision)
@@ -185,7 +195,8 @@ def tune_branching(problem, points, trees: int, seed: int = 0, precision: str = 
     n_cu = _n_cu()
 
     def run(cfg) -> float:
-        per_point = max(1, -(-int(trees) // cfg["chunk_paths"]))
+        item = cfg["chunk_paths"] if boundary is None else max(BVP_SPACE["chunk_paths"])
+        per_point = max(1, -(-int(trees) // item))
         want = items_per_wave * cfg["blocks_per_cu"] * 4 * n_cu
         k = int(min(n, max(1, -(-want // per_point))))
         idx = np.linspace(0, n - 1, k).round().astype(int)
@@ -202,7 +213,9 @@ def tune_branching(problem, points, trees: int, seed: int = 0, precision: str = 
         return _timed_rate(call, repeats)
 
     start = {k: s[k] for k in ("chunk_paths", "blocks_per_cu")}
-    best, r_best, r0 = _search(run, start, BRANCH_SPACE, log, kernel)
+    if boundary is not None and not s["tuned"]:
+        start["chunk_paths"] = BVP_ITEM
+    best, r_best, r0 = _search(run, start, BRANCH_SPACE if boundary is None else BVP_SPACE, log, kernel)
     best["refill_groups"] = 1
     _store(kernel, dim, precision, best)
     if log:

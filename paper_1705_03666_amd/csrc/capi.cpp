@@ -22,6 +22,7 @@
 #include "pdd_spec.hpp"
 #include "pdd_fixed.hpp"
 #include "pdd_tuning.hpp"
+#include "work_items.hpp"
 
 using namespace pdd;
 
@@ -628,30 +629,6 @@ Items make_items(int64_t n_nodes, const int64_t* counts, int64_t count_all, int 
     std::inplace_merge(r.q.begin() + (int64_t)n_big, r.q.begin() + (int64_t)mid, r.q.end(), longer);
   }
   return r;
-}
-
-// A branching call's items: about a point's last eighth in items of `small`
-// trees, the rest in items of `big`.
-TreeItems tree_items(int64_t n_points, int64_t trees, int64_t big, int64_t small) {
-  TreeItems t{};
-  t.n_points = (int32_t)n_points;
-  t.trees = (uint32_t)trees;
-  for (;; big *= 2, small *= 2) {
-    small = std::min(small, big);
-    const int64_t n_big = trees > big && small < big ? (trees - trees / 8) / big : 0;
-    const int64_t n_small = (trees - n_big * big + small - 1) / small;
-    if (n_points * (n_big + n_small) > (int64_t)INT32_MAX) continue;   // (slots are 32 bits)
-    t.n_big = (int32_t)n_big;
-    t.n_small = (int32_t)n_small;
-    t.big = (uint32_t)big;
-    t.small = (uint32_t)small;
-    return t;
-  }
-}
-std::vector<int64_t> first_slots(const TreeItems& t) {
-  std::vector<int64_t> first((size_t)t.n_points + 1);
-  for (size_t i = 0; i < first.size(); ++i) first[i] = (int64_t)i * (t.n_big + t.n_small);
-  return first;
 }
 
 // Cuts the queued items into pieces of at most `piece` paths, which keep the
@@ -1884,14 +1861,7 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
 
   const Tuning tune = choose_schedule(PDD_KERNEL_BRANCH_BVP, B.dim, fp32 ? PDD_FP32_STEP : PDD_FP64, o,
                                       device_cus(), n_points * trees);
-  // Trees stream across a wavefront's items, so short items cost it little
-  // and even out the wavefronts' ends: an eighth of a wavefront's share, from
-  // one tree per lane to 256 (1024 points x 10000 trees, 11 times: 33.0 ms
-  // with items of 2048, 28.7 of 512, 26.6 of 256; 27.0 with 64, whose sums
-  // and queue pops show).
-  const int64_t share = n_points * trees / ((int64_t)device_cus() * 128);
-  const int64_t piece = std::min<int64_t>(tune.chunk_paths, std::max<int64_t>(kWave, std::min<int64_t>(256, share)));
-  const TreeItems items = tree_items(n_points, trees, piece, std::max<int64_t>(kWave, piece / 8));
+  const TreeItems items = bvp_items(n_points, trees, tune, device_cus());
   const int n_items = items.count();
   BranchBvpLaunch& L = pl.bvl;
   L.P = &pl.bp;

@@ -9,8 +9,12 @@
 
 namespace pdd {
 
+// where a call's item size comes from
+enum ChunkFrom { kChunkDefault, kChunkTable, kChunkOption };
+
 struct Tuning {
   int chunk_paths;
+  ChunkFrom chunk_from;
   int piece_paths;   // forward walks: an item is run in pieces of at most this many paths
   int blocks_per_cu;
   int refill_groups;

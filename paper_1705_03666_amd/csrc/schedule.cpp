@@ -112,9 +112,10 @@ bool lookup(int kernel, int dim, int precision, Entry* out) {
 // CU (the FP32 branching kernels are built for four waves per SIMD, and
 // their LDS stacks allow four blocks), items of 16384 trees for k_branch
 // (C4: 3.36 ms against 3.60 with 8192 and 4.77 with 32768, measured when it
-// took 3.36; 2 blocks and 2048-tree items took 2.0x) and of at most 8192 trees
-// for k_branch_bvp, whose trees stream across items (run_branching_bvp cuts
-// them to 256 or less).
+// took 3.36; 2 blocks and 2048-tree items took 2.0x).  k_branch_bvp's trees
+// stream across items, whose size follows from the call where neither the
+// options nor the table give one (bvp_items, work_items.hpp): its 8192 here is
+// only what pdd_get_schedule reports.
 Entry defaults(int kernel, bool fp32, int dim) {
   (void)dim;
   if (kernel == PDD_KERNEL_BRANCH) return Entry{16384, fp32 ? 4 : 2, 1};
@@ -137,8 +138,12 @@ Tuning choose_schedule(int kernel, int dim, int precision, const pdd_options& o,
   const bool fp32 = precision == PDD_FP32_STEP;
   Entry e = defaults(kernel, fp32, dim);
   Entry tuned;
-  if (lookup(kernel, dim, precision, &tuned)) e = tuned;
   Tuning t;
+  t.chunk_from = kChunkDefault;
+  if (lookup(kernel, dim, precision, &tuned)) {
+    e = tuned;
+    t.chunk_from = kChunkTable;
+  }
   t.chunk_paths = e.chunk;
   t.blocks_per_cu = e.blocks;
   t.refill_groups = e.refill;
@@ -146,6 +151,7 @@ Tuning choose_schedule(int kernel, int dim, int precision, const pdd_options& o,
   if (o.refill_groups > 0) t.refill_groups = o.refill_groups;
   if (o.chunk_paths > 0) {
     t.chunk_paths = o.chunk_paths;
+    t.chunk_from = kChunkOption;
   } else {
     // a call too small for the item size: halve it (down to 1024 paths)
     // until every resident wavefront gets several items (the walks: four;
