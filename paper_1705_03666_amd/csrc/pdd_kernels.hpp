@@ -114,6 +114,15 @@ struct BranchBvpLaunch {
   double* rings;             // branch_ring_bytes(n_times) per wavefront
 };
 
+// Blocks of a launch that gives every group (node, item) a wavefront, in turns
+// of kGroupBlocks blocks: a launch has fewer than 2^32 threads, which 2^26
+// groups at once would reach.
+constexpr int64_t kGroupBlocks = 1 << 14;
+inline unsigned group_blocks(int64_t n) {
+  const int64_t per = kBlock / kWave, b = (n + per - 1) / per;
+  return (unsigned)(b < kGroupBlocks ? b : kGroupBlocks);
+}
+
 // Blocks of the launch's kernel that a compute unit holds at a time (0 if
 // that cannot be told).
 int walk_fwd_blocks(const WalkLaunch& L);

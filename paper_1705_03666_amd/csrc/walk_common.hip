@@ -33,15 +33,22 @@ __device__ __forceinline__ ItemStat merge_group(const ItemStat* __restrict__ s, 
   return r;
 }
 
+// The groups of a launch with a wavefront per group: the wavefront's first, and
+// how many the launch takes at a time (group_blocks).
+__device__ __forceinline__ int64_t first_group() {
+  return (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
+}
+__device__ __forceinline__ int64_t groups() { return (int64_t)gridDim.x * (kBlock / kWave); }
+
 // Merge the pieces' statistics into their items', one wavefront per item.
 __global__ void k_merge_pieces(const ItemStat* __restrict__ pstat, const MergeJob* __restrict__ jobs, int n_jobs,
                                ItemStat* __restrict__ istat) {
   const int lane = (int)(threadIdx.x & (kWave - 1));
-  const int i = (int)(blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave);
-  if (i >= n_jobs) return;
-  const MergeJob J = jobs[i];
-  const ItemStat r = merge_group(pstat + J.first, J.count, lane);
-  if (lane == 0) istat[J.item] = r;
+  for (int64_t i = first_group(); i < n_jobs; i += groups()) {
+    const MergeJob J = jobs[i];
+    const ItemStat r = merge_group(pstat + J.first, J.count, lane);
+    if (lane == 0) istat[J.item] = r;
+  }
 }
 
 // Merge item partials into per-node statistics, one wavefront per node.
@@ -49,17 +56,17 @@ __global__ void k_finalize_nodes(const ItemStat* __restrict__ istat, const int64
                                  int64_t n_nodes, const CallPtrs* __restrict__ cp, int64_t out_off,
                                  unsigned long long* __restrict__ counters) {
   const int lane = (int)(threadIdx.x & (kWave - 1));
-  const int64_t i = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave;
-  if (i >= n_nodes) return;
-  const int64_t f = first[i];
-  const ItemStat v = merge_group(istat + f, first[i + 1] - f, lane);
-  if (lane != 0) return;
-  pdd_node_stat_dev r;
-  r.mean = v.mean; r.m2 = v.m2; r.n = v.n; r.steps = v.steps; r.censored = v.censored;
-  ((pdd_node_stat_dev*)cp->out + out_off)[i] = r;
-  if (counters != nullptr) {
-    if (v.censored) atomicAdd(&counters[0], (unsigned long long)v.censored);
-    if (v.redrawn) atomicAdd(&counters[1], (unsigned long long)v.redrawn);
+  for (int64_t i = first_group(); i < n_nodes; i += groups()) {
+    const int64_t f = first[i];
+    const ItemStat v = merge_group(istat + f, first[i + 1] - f, lane);
+    if (lane != 0) continue;
+    pdd_node_stat_dev r;
+    r.mean = v.mean; r.m2 = v.m2; r.n = v.n; r.steps = v.steps; r.censored = v.censored;
+    ((pdd_node_stat_dev*)cp->out + out_off)[i] = r;
+    if (counters != nullptr) {
+      if (v.censored) atomicAdd(&counters[0], (unsigned long long)v.censored);
+      if (v.redrawn) atomicAdd(&counters[1], (unsigned long long)v.redrawn);
+    }
   }
 }
 
@@ -252,15 +259,13 @@ hipError_t launch_walk(const WalkLaunch& L, hipStream_t st) {
 
 hipError_t launch_merge_pieces(const ItemStat* pstat, const MergeJob* jobs, int n_jobs, ItemStat* istat,
                                hipStream_t st) {
-  const int blocks = (n_jobs + kBlock / kWave - 1) / (kBlock / kWave);
-  hipLaunchKernelGGL(k_merge_pieces, dim3((unsigned)blocks), dim3(kBlock), 0, st, pstat, jobs, n_jobs, istat);
+  hipLaunchKernelGGL(k_merge_pieces, dim3(group_blocks(n_jobs)), dim3(kBlock), 0, st, pstat, jobs, n_jobs, istat);
   return hipGetLastError();
 }
 
 hipError_t launch_finalize_nodes(const ItemStat* istat, const int64_t* first, int64_t n_nodes, const CallPtrs* cp,
                                  int64_t out_off, unsigned long long* counters, hipStream_t st) {
-  const int64_t blocks = (n_nodes + kBlock / kWave - 1) / (kBlock / kWave);
-  hipLaunchKernelGGL(k_finalize_nodes, dim3((unsigned)blocks), dim3(kBlock), 0, st, istat, first, n_nodes, cp,
+  hipLaunchKernelGGL(k_finalize_nodes, dim3(group_blocks(n_nodes)), dim3(kBlock), 0, st, istat, first, n_nodes, cp,
                      out_off, counters);
   return hipGetLastError();
 }

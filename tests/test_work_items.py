@@ -95,3 +95,12 @@ def test_boundary_item_sizes(ask):
     assert big == [256, 128, 300, 312, 1]
     # a small call: one tree per lane
     assert ask([f"bvp 5 3000 8192 0 {CUS}"])[0][1] == 64
+
+
+def test_a_wavefront_per_node_stays_below_the_launch_limit(ask):
+    """Calls take up to 2^30 nodes; a launch has fewer than 2^32 threads.  A
+    wavefront each, until the launch takes its groups in turns."""
+    sizes = [1, 4, 5, 4096, 65536, 65537, 2**26 - 1, 2**26, 2**30]
+    for n, (threads,) in zip(sizes, ask([f"groups {n}" for n in sizes])):
+        assert 0 < threads < 2**32 and threads % 256 == 0
+        assert threads >= 64 * min(n, 65536)

@@ -2,7 +2,8 @@
 // command a line from standard input and prints one line for each:
 //   trees <points> <trees> <big> <small>        tree_items
 //   bvp <points> <trees> <chunk> <from> <cus>   bvp_items (from: 0 default, 1 table, 2 option)
-// The answer is "<items a point> <big> <small> <covered>": covered is 1 if
+//   groups <n>                                  threads of a launch with a wavefront per group
+// The answer of the first two is "<items a point> <big> <small> <covered>": covered is 1 if
 // TreeItems::at deals every tree of every point out exactly once and every
 // slot once (0 if it does not, -1 if there are too many items to look).
 #include <hip/hip_runtime.h>
@@ -13,6 +14,7 @@
 #include <string>
 #include <vector>
 
+#include "pdd_kernels.hpp"
 #include "work_items.hpp"
 
 using namespace pdd;
@@ -47,7 +49,12 @@ int main() {
     std::istringstream in(line);
     std::string what;
     int64_t points, trees, a, b, cus = 0;
-    in >> what >> points >> trees >> a >> b;
+    in >> what >> points;
+    if (what == "groups") {
+      std::cout << (int64_t)group_blocks(points) * kBlock << std::endl;
+      continue;
+    }
+    in >> trees >> a >> b;
     TreeItems t{};
     if (what == "trees") {
       t = tree_items(points, trees, a, b);
