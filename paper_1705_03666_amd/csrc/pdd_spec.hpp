@@ -64,6 +64,12 @@ std::string spec_walk_name(bool fp32, int dim, int dfc, int layout, bool adjoint
 std::string spec_walk_source(const std::string& terms_src);
 std::string spec_branch_name(bool fp32, int dim, int layout, bool boundary);
 std::string spec_branch_source(const std::string& psi_src);
+// The key of a loaded kernel in the process's table, which every call with
+// generic terms looks up: short, as the target and the embedded headers are
+// the process's own.  And that of its entry on disk, which another build may
+// have written: with the target and the headers that the source includes.
+std::string spec_table_key(int dev, const std::string& name, const std::string& src);
+std::string spec_file_key(const std::string& arch, const std::string& name, const std::string& src);
 bool spec_compile(const std::string& src, const std::string& name, const std::string& arch, std::string* code,
                   std::string* lowered, std::string* err);
 

@@ -125,6 +125,30 @@ std::map<std::string, hipFunction_t> g_spec;   // (device, key) -> loaded kernel
 
 }  // namespace
 
+std::string spec_table_key(int dev, const std::string& name, const std::string& src) {
+  return std::to_string(dev) + "\n" + name + "\n" + src;
+}
+
+std::string spec_file_key(const std::string& arch, const std::string& name, const std::string& src) {
+  std::string key = arch + "\n" + name + "\n" + src;
+  // the embedded headers that the source includes, directly or through one
+  // another (an include of any other file is not compiled here)
+  std::vector<bool> in((size_t)kRtcHeaderCount, false);
+  std::vector<std::string> todo = {src};
+  while (!todo.empty()) {
+    const std::string text = todo.back();
+    todo.pop_back();
+    for (int i = 0; i < kRtcHeaderCount; ++i)
+      if (!in[(size_t)i] && text.find(std::string("#include \"") + kRtcHeaderNames[i] + "\"") != std::string::npos) {
+        in[(size_t)i] = true;
+        todo.push_back(kRtcHeaderBodies[i]);
+      }
+  }
+  for (int i = 0; i < kRtcHeaderCount; ++i)
+    if (in[(size_t)i]) key += std::string("\n") + kRtcHeaderBodies[i];
+  return key;
+}
+
 bool spec_compile(const std::string& src, const std::string& name, const std::string& arch, std::string* code,
                   std::string* lowered, std::string* err) {
   hiprtcProgram prog;
@@ -322,23 +346,20 @@ bool load_spec(const std::string& name, const std::string& src, hipFunction_t* f
     *err = "hipGetDevice failed";
     return false;
   }
+  std::lock_guard<std::mutex> lk(g_spec_mu);
+  const std::string mkey = spec_table_key(dev, name, src);
+  auto it = g_spec.find(mkey);
+  if (it != g_spec.end()) {
+    *fn = it->second;
+    return true;
+  }
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, dev) != hipSuccess) {
     *err = "hipGetDeviceProperties failed";
     return false;
   }
   const std::string arch = prop.gcnArchName;
-  // the key covers the generated source, the instantiation, the target and
-  // the embedded device headers
-  std::string key = arch + "\n" + name + "\n" + src;
-  for (int i = 0; i < kRtcHeaderCount; ++i) key += std::string("\n") + kRtcHeaderBodies[i];
-  std::lock_guard<std::mutex> lk(g_spec_mu);
-  const std::string mkey = std::to_string(dev) + "\n" + key;
-  auto it = g_spec.find(mkey);
-  if (it != g_spec.end()) {
-    *fn = it->second;
-    return true;
-  }
+  const std::string key = spec_file_key(arch, name, src);
   // disk cache: <hash>.pddjit holds the full key (compared on read), the
   // lowered kernel name and the code object
   const std::string dir = cache_dir();
