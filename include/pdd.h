@@ -302,7 +302,8 @@ pdd_status pdd_mc_interface(const pdd_linear_problem* problem, const double* nod
  * kernel, which computes the same values).  The schedule option is taken as
  * PDD_SCHED_PERSISTENT (no cached graph).  A call whose scratch does not fit
  * returns PDD_ERR_UNSUPPORTED before enqueuing anything, with the sizes in
- * pdd_last_error() (4096 nodes x 1e5 paths in FP32 take about 4 MB).
+ * pdd_last_error() (4096 nodes x 1e5 paths in FP32 need about 4 MB; a call
+ * uses more, here 8.5 MB, where that makes it faster and fits).
  * Every call on one device shares that device's area, whose contents are the
  * last call's: calls that overlap on one GPU (two streams, two threads) race
  * and must be serialised by the caller.  Arguments and errors otherwise as

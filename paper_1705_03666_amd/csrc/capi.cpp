@@ -371,9 +371,8 @@ pdd_status counters(unsigned long long** out) {
 // kernel launches (no memset, no copies), so it can be captured in a graph.
 // The caller's per-call pointers (node coordinates and coefficient arrays,
 // through the staging jobs; outputs and weights, through CallPtrs) are read
-// from the call block at the start of the arena, which is uploaded before
-// every launch: a graph plan is keyed on what shapes the launch, not on the
-// caller's buffers.
+// from the call block in the arena, which is uploaded before every launch: a
+// graph plan is keyed on what shapes the launch, not on the caller's buffers.
 struct Plan {
   int device = 0;
   void* arena = nullptr;
@@ -570,10 +569,6 @@ struct Items {
   std::vector<MergeJob> merge;
   int n_pieces = 0;
 };
-
-// Pieces that pdd_mc_interface_noalloc's fixed area takes (48 + 16 + 12 bytes
-// each, with the rest of a call's scratch next to them).
-constexpr int64_t kFixedPieces = 60000;
 
 // Work items, guided sizes.  A node's paths are cut into items of `chunk`
 // paths, except about its last eighth, which is cut into items of chunk / 8
@@ -949,8 +944,8 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
     for (int64_t i = 0; i < a.n_nodes; ++i) cost[(size_t)i] = est_steps(P, &hnodes[(size_t)i * dim], a.dt);
   }
   Items items;
+  std::vector<WorkItem> whole;   // the items before they are cut into pieces
   std::vector<int64_t> plain_first;
-  std::vector<PlainLaunch> plain_launches;
   int n_slots = 0;
   if (!plain) {
     items = make_items(a.n_nodes, a.paths, 0, tune.chunk_paths, cost);
@@ -962,30 +957,18 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
         if (!o.skip_items[w.slot]) keep.push_back(w);
       items.q.swap(keep);
     }
-    // (the fixed scratch area holds the pieces of small calls only)
-    if (!a.adjoint && (a.fixed == nullptr || total_paths / tune.piece_paths + n_slots <= kFixedPieces))
+    if (!a.adjoint) {
+      if (a.fixed != nullptr) whole = items.q;
       cut_items(tune.piece_paths, &items);
+    }
   }
   int n_items = (int)items.q.size();
-  pl.n_items = n_items;
-  pl.n_nodes = a.n_nodes;
 
-  // ---- arena layout
-  Arena U, A;   // what the host writes, in one copy; scratch after it
-  const size_t o_call = add_call_block(U, T.jobs.size() + 1);   // + the node-coordinate job
-  const size_t o_nodes = A.add(sizeof(double) * (size_t)a.n_nodes * (size_t)dim);
-  const size_t o_perm = U.add(sizeof(int32_t) * std::max<size_t>(1, T.perm.size()));
-  const size_t o_fac = U.add(sizeof(DevFactor) * std::max<size_t>(1, T.fac.size()));
-  const size_t o_cd = A.add(sizeof(double) * std::max(1, T.ncoef));
-  const size_t o_cf = A.add(sizeof(float) * std::max(1, T.ncoef));
-  const size_t o_q = A.add(sizeof(uint32_t) * 4);
-  size_t o_items = 0, o_istat = 0, o_first = 0, o_doff = 0;
-  std::vector<int64_t> doff((size_t)a.n_nodes + 1, 0);
-  for (int64_t i = 0; i < a.n_nodes; ++i) doff[(size_t)i + 1] = doff[(size_t)i] + a.paths[i];
-  int64_t n_stat = 0;
+  int64_t n_stat = n_slots;
   if (plain) {
     // forward: at most 4096 grid-striding blocks per node; adjoint: one path
     // per thread, one derivative row per block
+    n_stat = 0;
     plain_first.resize((size_t)a.n_nodes + 1);
     for (int64_t i = 0; i < a.n_nodes; ++i) {
       plain_first[(size_t)i] = n_stat;
@@ -999,17 +982,43 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
     if (a.adjoint) {
       items.first = plain_first;
       n_items = (int)n_stat;
-      pl.n_items = n_items;
     }
-  } else {
-    n_stat = n_slots;
-    o_items = U.add(sizeof(WorkItem) * std::max(1, n_items));
   }
-  o_istat = A.add(sizeof(ItemStat) * std::max<int64_t>(1, n_stat));
-  const size_t o_pstat = A.add(sizeof(ItemStat) * (size_t)items.n_pieces);
-  const size_t o_merge = U.add(sizeof(MergeJob) * items.merge.size());
-  o_first = U.add(sizeof(int64_t) * ((size_t)a.n_nodes + 1));
-  o_doff = U.add(sizeof(int64_t) * ((size_t)a.n_nodes + 1));
+  std::vector<int64_t> doff((size_t)a.n_nodes + 1, 0);
+  for (int64_t i = 0; i < a.n_nodes; ++i) doff[(size_t)i + 1] = doff[(size_t)i] + a.paths[i];
+
+  // ---- arena layout: scratch, then what the host writes, in one copy
+  Arena U, A;
+  size_t o_call, o_nodes, o_perm, o_fac, o_cd, o_cf, o_q, o_items, o_istat, o_pstat, o_merge, o_first, o_doff;
+  auto lay_out = [&] {
+    U = Arena();
+    A = Arena();
+    o_call = add_call_block(U, T.jobs.size() + 1);   // + the node-coordinate job
+    o_nodes = A.add(sizeof(double) * (size_t)a.n_nodes * (size_t)dim);
+    o_perm = U.add(sizeof(int32_t) * std::max<size_t>(1, T.perm.size()));
+    o_fac = U.add(sizeof(DevFactor) * std::max<size_t>(1, T.fac.size()));
+    o_cd = A.add(sizeof(double) * std::max(1, T.ncoef));
+    o_cf = A.add(sizeof(float) * std::max(1, T.ncoef));
+    o_q = A.add(sizeof(uint32_t) * 4);
+    o_items = plain ? 0 : U.add(sizeof(WorkItem) * std::max(1, n_items));
+    o_istat = A.add(sizeof(ItemStat) * std::max<int64_t>(1, n_stat));
+    o_pstat = items.n_pieces > 0 ? A.add(sizeof(ItemStat) * (size_t)items.n_pieces) : 0;
+    o_merge = items.n_pieces > 0 ? U.add(sizeof(MergeJob) * items.merge.size()) : 0;
+    o_first = U.add(sizeof(int64_t) * ((size_t)a.n_nodes + 1));
+    o_doff = U.add(sizeof(int64_t) * ((size_t)a.n_nodes + 1));
+  };
+  auto image_at = [&] { return (A.total + 255) & ~(size_t)255; };
+  lay_out();
+  if (a.fixed != nullptr && items.n_pieces > 0 && image_at() + U.total > a.fixed_bytes) {
+    // the pieces do not fit the fixed area: whole items take less
+    items.q.swap(whole);
+    items.merge.clear();
+    items.n_pieces = 0;
+    n_items = (int)items.q.size();
+    lay_out();
+  }
+  pl.n_items = n_items;
+  pl.n_nodes = a.n_nodes;
   // adjoint buffers
   const int NM = dfc >= 0 ? n_mono(dim, dfc) : 0;
   // generic terms anywhere in b, c, f select the term-capable kernels; for the
@@ -1065,7 +1074,7 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
   }
 
   // ---- allocate
-  const size_t scratch_at = (U.total + 255) & ~(size_t)255, total = scratch_at + A.total;
+  const size_t total = image_at() + U.total;
   ArenaLease lease;
   if (a.fixed != nullptr) {
     if (total > a.fixed_bytes)
@@ -1079,8 +1088,8 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
   } else {
     PDD_HIP(lease_arena(total, st, &lease, &pl.arena));
   }
-  char* base = (char*)pl.arena;
-  char* work = base + scratch_at;
+  char* work = (char*)pl.arena;
+  char* base = work + image_at();
   pl.d_call = (CallPtrs*)(base + o_call);
   pl.d_jobs = (StageJob*)(base + o_call + kJobsOff);
   pl.d_nodes = (double*)(work + o_nodes);

@@ -13,7 +13,7 @@ namespace pdd {
 constexpr int kMaxDevices = 64;
 // Scratch of pdd_mc_interface_noalloc: its staged tables, node copy, work
 // queue and per-item partials must fit (C5-sized forward calls, 4096 nodes x
-// 1e5 paths, take about 4 MB).
+// 1e5 paths, need about 4 MB, and 4.6 more to run their items in pieces).
 constexpr size_t kFixedScratchBytes = (size_t)16 << 20;
 
 // The current device's addresses of the fixed scratch area and of the two
