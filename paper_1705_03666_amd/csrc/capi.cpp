@@ -578,17 +578,16 @@ struct Items {
 // times of the wavefronts.  Slots stay node-major (a node's items are
 // consecutive), so per-node reductions run in a fixed order.  Within each
 // size class the queue is ordered longest first by `cost` when given.
-Items make_items(int64_t n_nodes, const int64_t* counts, int64_t count_all, int chunk, const std::vector<double>& cost) {
+Items make_items(int64_t n_nodes, const int64_t* paths, int chunk, const std::vector<double>& cost) {
   Items r;
   r.first.resize((size_t)n_nodes + 1);
   const int64_t big = std::max(1, chunk);
   const int64_t small = std::max<int64_t>(std::min<int64_t>(256, big), big / 8);
-  auto paths = [&](int64_t i) { return counts ? counts[i] : count_all; };
-  auto bigs = [&](int64_t i) { return paths(i) > big ? (paths(i) - paths(i) / 8) / big : 0; };
+  auto bigs = [&](int64_t i) { return paths[i] > big ? (paths[i] - paths[i] / 8) / big : 0; };
   int64_t n = 0;
   for (int64_t i = 0; i < n_nodes; ++i) {
     r.first[(size_t)i] = n;
-    n += bigs(i) + (paths(i) - bigs(i) * big + small - 1) / small;
+    n += bigs(i) + (paths[i] - bigs(i) * big + small - 1) / small;
   }
   r.first[(size_t)n_nodes] = n;
   r.slot_node.resize((size_t)n);
@@ -608,8 +607,8 @@ Items make_items(int64_t n_nodes, const int64_t* counts, int64_t count_all, int 
   for (int32_t i : order) {
     std::fill(r.slot_node.begin() + r.first[(size_t)i], r.slot_node.begin() + r.first[(size_t)i + 1], i);
     int32_t slot = (int32_t)(r.first[(size_t)i] + bigs(i));
-    for (int64_t p0 = bigs(i) * big; p0 < paths(i); p0 += small) {
-      const int64_t count = std::min(small, paths(i) - p0);
+    for (int64_t p0 = bigs(i) * big; p0 < paths[i]; p0 += small) {
+      const int64_t count = std::min(small, paths[i] - p0);
       (count < small && !cost.empty() ? rest : r.q)
           .push_back(WorkItem{i, (uint32_t)p0, (uint32_t)count, slot++});
     }
@@ -948,7 +947,7 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
   std::vector<int64_t> plain_first;
   int n_slots = 0;
   if (!plain) {
-    items = make_items(a.n_nodes, a.paths, 0, tune.chunk_paths, cost);
+    items = make_items(a.n_nodes, a.paths, tune.chunk_paths, cost);
     n_slots = (int)items.q.size();
     if (o.skip_items) {
       // resume: queue only the items not skipped; all slots stay in place
@@ -1380,7 +1379,7 @@ pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
   std::vector<double> cost((size_t)a.n_nodes);
   for (int64_t i = 0; i < a.n_nodes; ++i)
     cost[(size_t)i] = est_steps(a.probs[a.node_prob[i]], &hnodes[(size_t)i * 3], a.dt);
-  Items items = make_items(a.n_nodes, a.paths, 0, tune.chunk_paths, cost);
+  Items items = make_items(a.n_nodes, a.paths, tune.chunk_paths, cost);
   const int n_slots = (int)items.q.size();
   std::vector<BatchQueue> queues = order_by_problem(a, cost, &items.q);
   cut_items(tune.piece_paths, &items);
@@ -2112,7 +2111,7 @@ int64_t pdd_item_count(int32_t kernel, int32_t dim, int64_t n_nodes, const int64
     }
     const Tuning tune = choose_schedule(kernel, dim, o.precision == PDD_FP32_STEP ? PDD_FP32_STEP : PDD_FP64, o,
                                         device_cus(), total);
-    return (int64_t)make_items(n_nodes, paths_host, 0, tune.chunk_paths, {}).q.size();
+    return (int64_t)make_items(n_nodes, paths_host, tune.chunk_paths, {}).q.size();
   } catch (const std::bad_alloc&) {
     return fail(PDD_ERR_NO_MEMORY, "host allocation failed");
   } catch (...) {
