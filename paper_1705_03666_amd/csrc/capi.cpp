@@ -345,15 +345,6 @@ int device_cus() {
   return cus[dev];
 }
 
-// Blocks of a persistent launch: as many per compute unit as asked for, but no
-// more than it holds at a time (`held`, where wavefronts start on items of
-// their own; else 0) and no more than there are items for.
-int persistent_grid(int blocks_per_cu, int held, int n_items) {
-  const int per_cu = held > 0 ? std::min(held, blocks_per_cu) : blocks_per_cu;
-  const int need = (n_items + kBlock / kWave - 1) / (kBlock / kWave);
-  return std::max(1, std::min(per_cu * device_cus(), need));
-}
-
 // per-device warning counters (censored paths, redrawn trees): a device
 // array of the library (zero when the library is loaded), never allocated
 std::mutex g_mu;
@@ -1192,7 +1183,7 @@ pdd_status run_linear(const LinearPlanArgs& a, hipStream_t st) {
     L.adjoint = a.adjoint;
     L.wos = a.wos;
     L.spec = spec;
-    L.grid = persistent_grid(tune.blocks_per_cu, a.adjoint ? 0 : walk_fwd_blocks(L), n_items);
+    L.grid = persistent_grid(tune.blocks_per_cu, a.adjoint ? 0 : walk_fwd_blocks(L), n_items, device_cus());
     L.items = (const WorkItem*)(base + o_items);
     L.n_items = n_items;
     L.qhead = pl.d_qhead;
@@ -1384,7 +1375,7 @@ pdd_status run_linear_batch(const BatchArgs& a, hipStream_t st) {
   std::vector<BatchQueue> queues = order_by_problem(a, cost, &items.q);
   cut_items(tune.piece_paths, &items);
   const int n_items = (int)items.q.size();
-  const int grid = persistent_grid(tune.blocks_per_cu, walk_batch_blocks(fp32, o.rng_layout, a.wos), n_items);
+  const int grid = persistent_grid(tune.blocks_per_cu, walk_batch_blocks(fp32, o.rng_layout, a.wos), n_items, device_cus());
   place_queues(a, items.q, grid * (kBlock / kWave), &queues);
   pl.n_items = n_items;
   pl.n_nodes = a.n_nodes;
@@ -1722,7 +1713,7 @@ pdd_status run_branching(const pdd_branching_problem* Bp, const double* points, 
   BL.fp32 = fp32;
   BL.layout = o.rng_layout;
   BL.spec = spec;
-  const int grid = persistent_grid(tune.blocks_per_cu, branch_blocks(BL), n_items);
+  const int grid = persistent_grid(tune.blocks_per_cu, branch_blocks(BL), n_items, device_cus());
   const int64_t spill_entries = std::max(0, B.max_segments - branch_lds_depth(fp32));
 
   Arena U, A;   // what the host writes, in one copy; scratch after it
@@ -1877,7 +1868,7 @@ pdd_status run_branching_bvp(const pdd_branching_problem* Bp, const pdd_branchin
   L.fp32 = fp32;
   L.layout = o.rng_layout;
   L.spec = spec;
-  const int grid = persistent_grid(tune.blocks_per_cu, branch_bvp_blocks(L), n_items);
+  const int grid = persistent_grid(tune.blocks_per_cu, branch_bvp_blocks(L), n_items, device_cus());
   const int64_t spill_entries = std::max(0, B.max_segments - branch_lds_depth(fp32));
 
   Arena U, A;   // what the host writes, in one copy; scratch after it

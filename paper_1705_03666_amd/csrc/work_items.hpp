@@ -1,4 +1,5 @@
-// Work items of a branching call (host arithmetic only).
+// Grids of the persistent launches and the work items of a branching call (host
+// arithmetic only).
 #pragma once
 #include <stdint.h>
 
@@ -9,6 +10,15 @@
 #include "pdd_tuning.hpp"
 
 namespace pdd {
+
+// Blocks of a persistent launch: as many per compute unit as asked for, but no
+// more than it holds at a time (`held`, where wavefronts start on items of
+// their own; else 0) and no more than there are items for.
+inline int persistent_grid(int blocks_per_cu, int held, int n_items, int n_cus) {
+  const int per_cu = held > 0 ? std::min(held, blocks_per_cu) : blocks_per_cu;
+  const int per = kBlock / kWave, need = n_items / per + (n_items % per != 0 ? 1 : 0);
+  return std::max(1, std::min(per_cu * n_cus, need));
+}
 
 // A branching call's items: about a point's last eighth in items of `small`
 // trees, the rest in items of `big`.

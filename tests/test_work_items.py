@@ -104,3 +104,12 @@ def test_a_wavefront_per_node_stays_below_the_launch_limit(ask):
     for n, (threads,) in zip(sizes, ask([f"groups {n}" for n in sizes])):
         assert 0 < threads < 2**32 and threads % 256 == 0
         assert threads >= 64 * min(n, 65536)
+
+
+def test_grids(ask):
+    """A block for four items, as many as the chip holds of those asked for, at
+    least one; up to the largest number of items."""
+    for (per_cu, held, items), want in (((8, 5, 0), 1), ((8, 5, 1), 1), ((8, 5, 5), 2), ((8, 5, 10**6), 5 * CUS),
+                                        ((2, 5, 10**6), 2 * CUS), ((8, 0, 10**6), 8 * CUS),
+                                        ((4, 4, 2**31 - 1), 4 * CUS), ((4, 4, 2**31 - 3), 4 * CUS)):
+        assert ask([f"grid {per_cu} {held} {items} {CUS}"]) == [[want]], (per_cu, held, items)

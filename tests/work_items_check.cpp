@@ -2,10 +2,12 @@
 // command a line from standard input and prints one line for each:
 //   trees <points> <trees> <big> <small>        tree_items
 //   bvp <points> <trees> <chunk> <from> <cus>   bvp_items (from: 0 default, 1 table, 2 option)
+//   grid <blocks a CU> <held> <items> <cus>     persistent_grid
 //   groups <n>                                  threads of a launch with a wavefront per group
-// The answer of the first two is "<items a point> <big> <small> <covered>": covered is 1 if
-// TreeItems::at deals every tree of every point out exactly once and every
-// slot once (0 if it does not, -1 if there are too many items to look).
+// The answer of the first two is "<items a point> <big> <small> <covered>":
+// covered is 1 if TreeItems::at deals every tree of every point out exactly
+// once and every slot once (0 if it does not, -1 if there are too many items
+// to look); that of the others is one number.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -52,6 +54,11 @@ int main() {
     in >> what >> points;
     if (what == "groups") {
       std::cout << (int64_t)group_blocks(points) * kBlock << std::endl;
+      continue;
+    }
+    if (what == "grid") {
+      in >> trees >> a >> b;
+      std::cout << persistent_grid((int)points, (int)trees, (int)a, (int)b) << std::endl;
       continue;
     }
     in >> trees >> a >> b;
