@@ -141,8 +141,8 @@ struct BatchProblem {
 // A wavefront streams through the queue of one problem (whose dimension and
 // domain kind its code is instantiated for), then goes on to the next
 // problem's queue.  The wavefronts start spread over the problems by their
-// share of the estimated work (`start`: the first wavefront of every problem),
-// so the queues run out together and few wavefronts drain twice.
+// share of the estimated work (BatchQueue::first_wave: the first wavefront of
+// every problem), so the queues run out together and few wavefronts drain twice.
 // FP32: built for six waves per SIMD (at most 80 VGPRs), so the default six
 // blocks per CU are all resident.
 template <typename R, int LAYOUT, bool WOS>

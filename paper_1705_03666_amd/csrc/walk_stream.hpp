@@ -19,9 +19,10 @@
 // ended: with 1024 positions and 64 lanes that is a path of 15 mean lengths.
 //
 // Draining.  When the queue is empty and at most a quarter (half, where a
-// path's draws allow it) of the lanes still run a path, the idle lanes draw for the running ones: the generator is
-// counter-based, so a path's next L blocks are drawn by L lanes at once, pass
-// through LDS, and the path's own lane is left with the steps.  What bounds a
+// path's draws allow it) of the lanes still run a path, the idle lanes draw for
+// the running ones: the generator is counter-based, so a path's next L blocks
+// are drawn by L lanes at once, pass through LDS, and the path's own lane is
+// left with the steps.  What bounds a
 // small call (and the end of a large one) is the longest path's chain of
 // dependent instructions, most of which are the ten Philox rounds and
 // Box-Muller: 7 nodes x 300 paths on an interval took 300 cycles a step of
@@ -163,7 +164,8 @@ struct StreamArgs {
 // problem's) first n_first wavefronts start with the item of their own number
 // `first` (none if it is n_first), the rest of the queue is popped: with one
 // item per wavefront or less, the queue's atomic, on which all wavefronts
-// would otherwise start (70000 cycles for 2500 of them), is not touched.  PROB gives the problem:
+// would otherwise start (70000 cycles for 2500 of them), is not touched.  PROB
+// gives the problem:
 //   kWos, kFree (pure diffusion: b = c = f = 0), kYZ (records carry Y and Z),
 //   kRoll (heavy steps: one copy of the step's code, in a loop that reads its
 //   Gaussians from LDS; unrolled, FP64 steps with generic terms took 90 KB of
@@ -175,7 +177,8 @@ struct StreamArgs {
 //   step(X, Y, Z, z): one Euler step with drift, killing and source
 //   g(x): the boundary data
 template <typename R, int DIM, int LAYOUT, class PROB, class LDS>
-__device__ __forceinline__ void stream_walk(const PROB& prob, const StreamArgs& A, LDS* L, int lane, uint32_t first, uint32_t n_first) {
+__device__ __forceinline__ void stream_walk(const PROB& prob, const StreamArgs& A, LDS* L, int lane, uint32_t first,
+                                            uint32_t n_first) {
   using NZr = Normals<R, LAYOUT>;
   using GS = GroupShape<DIM, NZr::kPerBlock>;
   constexpr int PB = NZr::kPerBlock;
@@ -739,8 +742,9 @@ struct SingleProblem {
 };
 
 // Occupancy request: the FP32 kernels without generic terms fit in 80 VGPRs
-// (pure diffusion, walk on spheres: six waves per SIMD) or 128 (four), those
-// with terms in 256; the FP64 kernels are left unconstrained.
+// (pure diffusion, walk on spheres: six waves per SIMD) or, with a polynomial
+// part, in 96 (five), those with terms in 256 (two); the FP64
+// kernels are left unconstrained.
 template <typename R, int DFC, bool TERMS>
 constexpr int fwd_min_waves() { return sizeof(R) == 4 ? (TERMS ? 2 : (DFC < 0 ? 6 : 5)) : 1; }
 
